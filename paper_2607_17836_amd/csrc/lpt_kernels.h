@@ -190,13 +190,15 @@ hipError_t launch_interp32(const StepParams &P, const float4 *rec, int scheme, i
                            const double *x, const double *y, double wa, double wb, double *u,
                            double *v, hipStream_t st);
 
-// Readout in original particle order (id - offset).
-hipError_t launch_readout64(const State64 &S, const double2 *x0, int64_t offset, int64_t count,
-                            double L, double *xw, double *yw, double *xu, double *yu,
-                            double *vx, double *vy, hipStream_t st);
-hipError_t launch_readout32(const StepParams &P, const State32 &S, int64_t offset, int64_t count,
-                            double *xw, double *yw, double *xu, double *yu, double *vx,
-                            double *vy, hipStream_t st);
+// Readout in original particle order (id - offset).  spare: the state buffer
+// not in use, overwritten as scratch; reordered: whether the slots may be out
+// of original order (a hint for the choice of kernels, not for the results).
+hipError_t launch_readout64(const State64 &S, const State64 &spare, const double2 *x0,
+                            int64_t offset, int64_t count, bool reordered, double *xw, double *yw,
+                            double *xu, double *yu, double *vx, double *vy, hipStream_t st);
+hipError_t launch_readout32(const StepParams &P, const State32 &S, const State32 &spare,
+                            int64_t offset, int64_t count, bool reordered, double *xw, double *yw,
+                            double *xu, double *yu, double *vx, double *vy, hipStream_t st);
 
 hipError_t launch_order(const uint32_t *id, int64_t offset, int64_t count, int32_t *out,
                         hipStream_t st);

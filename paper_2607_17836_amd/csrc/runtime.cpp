@@ -106,6 +106,8 @@ struct lpt_ctx {
     int32_t sort_cells = 2;  // 1: the key also orders cells inside each tile; 2: on
                              // the first re-sort only
     bool sorted_once = false;   // a re-sort has put the present particles in order
+    bool ever_sorted = false;   // the slots may be out of original order (only a hint
+                                // for the readout, which follows the ids either way)
     int32_t tile_cap = 0;    // LDS tile capacity of the step kernel, node records
     int32_t tile_auto = 0;   // 1: step launches size the tile to their occupancy
     int32_t rows = 1;        // FP32 bilinear tracer step: particles per thread
@@ -222,15 +224,33 @@ int ilog2i(int64_t v)
     return s;
 }
 
+// The two arrays that hold a particle's position (pos and disp, or uc and
+// off) are one allocation, the second right behind the first, so that the
+// buffer a step is not using is also a scratch of one whole record per
+// particle (see readout).
+template <typename A, typename B>
+hipError_t alloc_pair(A *&a, B *&b, size_t count)
+{
+    static_assert(sizeof(A) == sizeof(B), "two arrays of one element size");
+    const hipError_t e = dalloc(a, 2 * count);
+    b = a ? reinterpret_cast<B *>(a + count) : nullptr;
+    return e;
+}
+
+template <typename A, typename B>
+void free_pair(A *&a, B *&b)
+{
+    dfree(a);
+    b = nullptr;
+}
+
 void free_state(lpt_ctx *c)
 {
     for (int k = 0; k < 2; ++k) {
-        dfree(c->s64[k].pos);
-        dfree(c->s64[k].disp);
+        free_pair(c->s64[k].pos, c->s64[k].disp);
         dfree(c->s64[k].vel);
         dfree(c->s64[k].id);
-        dfree(c->s32[k].uc);
-        dfree(c->s32[k].off);
+        free_pair(c->s32[k].uc, c->s32[k].off);
         dfree(c->s32[k].vel);
         dfree(c->s32[k].id);
     }
@@ -421,7 +441,7 @@ lpt_status do_sort(lpt_ctx *c, const uint32_t **perm_out = nullptr,
     // where it fits in 32 bits; tiles only otherwise
     bool cells = c->sort_cells == 1 || (c->sort_cells == 2 && !c->sorted_once);
     if (cells && key_width(c->n, c->sort_tile, 1, (int)c->sp.size()) > 32) cells = false;
-    c->sorted_once = true;
+    c->sorted_once = c->ever_sorted = true;
     const int kb = std::max(1, key_width(c->n, c->sort_tile, cells, (int)c->sp.size()));
     if (c->precision == LPT_FP64)
         HIP_TRY(c, launch_keys64(P, c->s64[c->cur], c->sort_tile, tb, cells, kb, c->sw,
@@ -748,8 +768,8 @@ lpt_status grow_state(lpt_ctx *c, int64_t np, int64_t old, bool inertial)
     double2 *nx0 = nullptr, *nv0 = nullptr;
     auto cleanup = [&]() {
         for (int k = 0; k < 2; ++k) {
-            dfree(n64[k].pos); dfree(n64[k].disp); dfree(n64[k].vel); dfree(n64[k].id);
-            dfree(n32[k].uc); dfree(n32[k].off); dfree(n32[k].vel); dfree(n32[k].id);
+            free_pair(n64[k].pos, n64[k].disp); dfree(n64[k].vel); dfree(n64[k].id);
+            free_pair(n32[k].uc, n32[k].off); dfree(n32[k].vel); dfree(n32[k].id);
         }
         dfree(nx0);
         dfree(nv0);
@@ -758,11 +778,11 @@ lpt_status grow_state(lpt_ctx *c, int64_t np, int64_t old, bool inertial)
     const bool vel = inertial || c->has_inertial;
     for (int k = 0; k < 2 && ok; ++k) {
         if (fp64) {
-            ok = dalloc(n64[k].pos, np) == hipSuccess && dalloc(n64[k].disp, np) == hipSuccess &&
+            ok = alloc_pair(n64[k].pos, n64[k].disp, np) == hipSuccess &&
                  dalloc(n64[k].id, np) == hipSuccess &&
                  (!vel || dalloc(n64[k].vel, np) == hipSuccess);
         } else {
-            ok = dalloc(n32[k].uc, np) == hipSuccess && dalloc(n32[k].off, np) == hipSuccess &&
+            ok = alloc_pair(n32[k].uc, n32[k].off, np) == hipSuccess &&
                  dalloc(n32[k].id, np) == hipSuccess &&
                  (!vel || dalloc(n32[k].vel, np) == hipSuccess);
         }
@@ -1547,12 +1567,17 @@ lpt_status readout(lpt_ctx *c, int32_t sid, double *xw, double *yw, double *xu, 
             st.bufs.push_back(dev[k]);
         }
     }
+    // the other state buffer holds nothing between calls: scratch for a
+    // readout out of cell order
+    const bool sorted = c->ever_sorted;
     if (c->precision == LPT_FP64)
-        HIP_TRY(c, launch_readout64(c->s64[c->cur], c->x0, s.offset, s.count, c->L, dev[0], dev[1],
-                                    dev[2], dev[3], dev[4], dev[5], c->stream));
+        HIP_TRY(c, launch_readout64(c->s64[c->cur], c->s64[1 - c->cur], c->x0, s.offset, s.count,
+                                    sorted, dev[0], dev[1], dev[2], dev[3], dev[4], dev[5],
+                                    c->stream));
     else
-        HIP_TRY(c, launch_readout32(make_params(c), c->s32[c->cur], s.offset, s.count, dev[0],
-                                    dev[1], dev[2], dev[3], dev[4], dev[5], c->stream));
+        HIP_TRY(c, launch_readout32(make_params(c), c->s32[c->cur], c->s32[1 - c->cur], s.offset,
+                                    s.count, sorted, dev[0], dev[1], dev[2], dev[3], dev[4],
+                                    dev[5], c->stream));
     if (!on_device) {
         for (int k = 0; k < 6; ++k)
             if (outs[k])
@@ -1988,6 +2013,7 @@ lpt_status lpt_set_state(lpt_ctx *c, const void *blob, size_t size)
     c->nrec = h.nrec;
     c->time_mode = h.time_mode;
     c->sorted_once = h.sorted_once != 0;
+    c->ever_sorted = true;   // the blob's slots come in its own order
     c->ck_valid = false;
     invalidate_graphs(c);
     return LPT_OK;
