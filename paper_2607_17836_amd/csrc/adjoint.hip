@@ -284,9 +284,9 @@ __global__ __launch_bounds__(kMaxBlock) void recompute64_kernel(StepParams P,
     const double2 *planes = reinterpret_cast<const double2 *>(lpt_dyn_lds);
     double ddx, ddy;
     if (!CUBIC || sp.scheme == kBilinear)
-        rk4_tracer64<false>(rec0, planes, T, P, sp.scheme, x, ddx, ddy);
+        rk4_tracer64<false>(rec0, planes, T, P, P.w, sp.scheme, x, ddx, ddy);
     else
-        rk4_tracer64<true>(rec0, planes, T, P, sp.scheme, x, ddx, ddy);
+        rk4_tracer64<true>(rec0, planes, T, P, P.w, sp.scheme, x, ddx, ddy);
     out[p] = make_double2(wrap_pos(x.x + ddx, P.L), wrap_pos(x.y + ddy, P.L));
 }
 
@@ -378,15 +378,15 @@ __global__ __launch_bounds__(kMaxBlock) void adjoint64_kernel(StepParams P,
         double k1x, k1y, k2x, k2y, k3x, k3y;
         px[0] = x.x;
         py[0] = x.y;
-        vel64<CUBIC>(rec0, planes, T, P, scheme, px[0], py[0], P.wa[0], P.wb[0], P.smode[0],
+        vel64<CUBIC>(rec0, planes, T, P, scheme, px[0], py[0], P.w.wa[0], P.w.wb[0], P.w.smode[0],
                      k1x, k1y);
         px[1] = x.x + hdt * k1x;
         py[1] = x.y + hdt * k1y;
-        vel64<CUBIC>(rec0, planes, T, P, scheme, px[1], py[1], P.wa[1], P.wb[1], P.smode[1],
+        vel64<CUBIC>(rec0, planes, T, P, scheme, px[1], py[1], P.w.wa[1], P.w.wb[1], P.w.smode[1],
                      k2x, k2y);
         px[2] = x.x + hdt * k2x;
         py[2] = x.y + hdt * k2y;
-        vel64<CUBIC>(rec0, planes, T, P, scheme, px[2], py[2], P.wa[2], P.wb[2], P.smode[2],
+        vel64<CUBIC>(rec0, planes, T, P, scheme, px[2], py[2], P.w.wa[2], P.w.wb[2], P.w.smode[2],
                      k3x, k3y);
         px[3] = x.x + dt * k3x;
         py[3] = x.y + dt * k3y;
@@ -420,13 +420,13 @@ __global__ __launch_bounds__(kMaxBlock) void adjoint64_kernel(StepParams P,
             if (!CUBIC || bilinear_at(P, scheme, loc)) {
                 const Sten64<2> st = stencil64<2>(scheme, loc);
                 if (grid)
-                    scatter64<2, DET>(G, P, st, grp, P.wa[q], P.wb[q], lk[0][q][0], lk[0][q][1]);
-                jacobian64<2>(rec0, planes, T, P, st, P.wa[q], P.wb[q], P.smode[q], J);
+                    scatter64<2, DET>(G, P, st, grp, P.w.wa[q], P.w.wb[q], lk[0][q][0], lk[0][q][1]);
+                jacobian64<2>(rec0, planes, T, P, st, P.w.wa[q], P.w.wb[q], P.w.smode[q], J);
             } else if constexpr (CUBIC) {
                 const Sten64<4> st = stencil64<4>(scheme, loc);
                 if (grid)
-                    scatter64<4, DET>(G, P, st, grp, P.wa[q], P.wb[q], lk[0][q][0], lk[0][q][1]);
-                jacobian64<4>(rec0, planes, T, P, st, P.wa[q], P.wb[q], P.smode[q], J);
+                    scatter64<4, DET>(G, P, st, grp, P.w.wa[q], P.w.wb[q], lk[0][q][0], lk[0][q][1]);
+                jacobian64<4>(rec0, planes, T, P, st, P.w.wa[q], P.w.wb[q], P.w.smode[q], J);
             }
 #pragma unroll
             for (int r = 0; r < NL; ++r) {
@@ -470,8 +470,8 @@ __global__ __launch_bounds__(kMaxBlock) void adjoint64_kernel(StepParams P,
                 const double *acc = static_cast<const double *>(G.acc);
                 double *out = static_cast<double *>(gU);
                 // time levels 0, 1, 2 were taken at the weights of stages 0, 1, 3
-                const double wa[3] = {P.wa[0], P.wa[1], P.wa[3]};
-                const double wb[3] = {P.wb[0], P.wb[1], P.wb[3]};
+                const double wa[3] = {P.w.wa[0], P.w.wa[1], P.w.wa[3]};
+                const double wb[3] = {P.w.wb[0], P.w.wb[1], P.w.wb[3]};
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
                     double s0 = 0.0, s1 = 0.0;

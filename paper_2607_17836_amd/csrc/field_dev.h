@@ -306,6 +306,30 @@ __device__ __forceinline__ double dpp_f64(double x)
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
+// Lane groups of four (the small launches' bicubic stencils, one row a lane):
+// the value of lane B of the caller's group.  All four lanes must be active.
+template <int B>
+__device__ __forceinline__ double quad_lane(double x) { return dpp_f64<B * 0x55, 0xF>(x); }
+template <int B>
+__device__ __forceinline__ float quad_lane(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x),
+                                                                 B * 0x55, 0xF, 0xF, true));
+}
+
+// w[0] r0 + w[1] r1 + w[2] r2 + w[3] r3 with r_b the r of the group's lane b, in
+// the order in which one lane sums the rows of a stencil.
+template <typename T>
+__device__ __forceinline__ T quad_rows(const T w[4], T r)
+{
+    T a = T(0);
+    a += w[0] * quad_lane<0>(r);
+    a += w[1] * quad_lane<1>(r);
+    a += w[2] * quad_lane<2>(r);
+    a += w[3] * quad_lane<3>(r);
+    return a;
+}
+
 // Exchanges of 64-bit lane values between lane groups (gfx950 permlane
 // swaps, one per 32-bit half).  swap32: x takes [x lanes 0-31 | y lanes
 // 0-31], y takes [x lanes 32-63 | y lanes 32-63].  swap16, per 16-lane row r:
@@ -650,10 +674,31 @@ __device__ __forceinline__ void cub64(const Nodes &N, const double wx[4], const 
     v = av;
 }
 
+// cub64 by a group of four lanes, one row of the stencil each: the same sums in
+// the same order, so the same bits in every lane of the group.
+template <typename Nodes>
+__device__ __forceinline__ void cub64_quad(const Nodes &N, const double wx[4], const double wy[4],
+                                           int smode, double wa, double wb, double &u, double &v)
+{
+    const int b = (int)threadIdx.x & 3;
+    double ru = 0.0, rv = 0.0;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        double nu, nv;
+        N.get(a, b, smode, wa, wb, nu, nv);
+        ru += wx[a] * nu;
+        rv += wx[a] * nv;
+    }
+    u = quad_rows(wy, ru);
+    v = quad_rows(wy, rv);
+}
+
 // Velocity at (x, y) (physical units, any real value) with temporal weights
 // (wa, wb) on the two snapshot slots.  rec0 points at global node (0, 0);
 // tile/T is the block's LDS tile, two planes (T.on == 0: global only).
-template <bool CUBIC>
+// LANES: lanes that evaluate one point together (4: a bicubic stencil is
+// split over them by rows), all with the same arguments.
+template <bool CUBIC, int LANES = 1>
 __device__ __forceinline__ void vel64(const Rec64 *__restrict__ rec0, const double2 *tile,
                                       const Tile &T, const StepParams &P, int scheme, double x,
                                       double y, double wa, double wb, int smode, double &u,
@@ -682,7 +727,10 @@ __device__ __forceinline__ void vel64(const Rec64 *__restrict__ rec0, const doub
             weights_bs(xi, wx);
             weights_bs(eta, wy);
         }
-        if (tile_index(T, i - 1, j - 1, 4, n, mask, t))
+        if constexpr (LANES == 4)
+            cub64_quad(RecNodes64{rec0 + (__mul24(j - 1, P.pitch) + (i - 1)), P.pitch}, wx, wy,
+                       smode, wa, wb, u, v);
+        else if (tile_index(T, i - 1, j - 1, 4, n, mask, t))
             cub64(TileNodes64{tile + t, T.w, T.w * T.h}, wx, wy, smode, wa, wb, u, v);
         else
             cub64(RecNodes64{rec0 + (__mul24(j - 1, P.pitch) + (i - 1)), P.pitch}, wx, wy, smode,
@@ -705,25 +753,58 @@ __device__ __forceinline__ double wrap_pos(double z, double L)
 }
 
 // Displacement of one tracer over one RK4 step from x (eq. rk4_update, stages
-// at t_n, t_n + dt/2, t_n + dt/2, t_n + dt with the temporal weights of P).
-// The step kernel and the adjoint's recomputation share it, so recomputed
+// at t_n, t_n + dt/2, t_n + dt/2, t_n + dt with the temporal weights W).
+// The step kernels and the adjoint's recomputation share it, so recomputed
 // trajectories repeat the forward ones bit for bit.
-template <bool CUBIC>
+template <bool CUBIC, int LANES = 1>
 __device__ __forceinline__ void rk4_tracer64(const Rec64 *__restrict__ rec0, const double2 *tile,
-                                             const Tile &T, const StepParams &P, int scheme,
-                                             double2 x, double &ddx, double &ddy)
+                                             const Tile &T, const StepParams &P,
+                                             const StageWeights &W, int scheme, double2 x,
+                                             double &ddx, double &ddy)
 {
     const double dt = P.dt, hdt = 0.5 * P.dt, dt6 = P.dt / 6.0;
     double k1x, k1y, k2x, k2y, k3x, k3y, k4x, k4y;
-    vel64<CUBIC>(rec0, tile, T, P, scheme, x.x, x.y, P.wa[0], P.wb[0], P.smode[0], k1x, k1y);
-    vel64<CUBIC>(rec0, tile, T, P, scheme, x.x + hdt * k1x, x.y + hdt * k1y, P.wa[1], P.wb[1],
-                 P.smode[1], k2x, k2y);
-    vel64<CUBIC>(rec0, tile, T, P, scheme, x.x + hdt * k2x, x.y + hdt * k2y, P.wa[2], P.wb[2],
-                 P.smode[2], k3x, k3y);
-    vel64<CUBIC>(rec0, tile, T, P, scheme, x.x + dt * k3x, x.y + dt * k3y, P.wa[3], P.wb[3],
-                 P.smode[3], k4x, k4y);
+    vel64<CUBIC, LANES>(rec0, tile, T, P, scheme, x.x, x.y, W.wa[0], W.wb[0], W.smode[0], k1x,
+                        k1y);
+    vel64<CUBIC, LANES>(rec0, tile, T, P, scheme, x.x + hdt * k1x, x.y + hdt * k1y, W.wa[1],
+                        W.wb[1], W.smode[1], k2x, k2y);
+    vel64<CUBIC, LANES>(rec0, tile, T, P, scheme, x.x + hdt * k2x, x.y + hdt * k2y, W.wa[2],
+                        W.wb[2], W.smode[2], k3x, k3y);
+    vel64<CUBIC, LANES>(rec0, tile, T, P, scheme, x.x + dt * k3x, x.y + dt * k3y, W.wa[3],
+                        W.wb[3], W.smode[3], k4x, k4y);
     ddx = dt6 * (k1x + 2.0 * k2x + 2.0 * k3x + k4x);
     ddy = dt6 * (k1y + 2.0 * k2y + 2.0 * k3y + k4y);
+}
+
+// The same for an inertial particle of velocity vn (eqs. inertial_particle,
+// drag_rk4, rk4_inertial; is = 1 / St), whose velocity is advanced too.
+template <bool CUBIC, int LANES = 1>
+__device__ __forceinline__ void rk4_inertial64(const Rec64 *__restrict__ rec0, const double2 *tile,
+                                               const Tile &T, const StepParams &P,
+                                               const StageWeights &W, int scheme, double is,
+                                               double2 x, double2 &vn, double &ddx, double &ddy)
+{
+    const double dt = P.dt, hdt = 0.5 * P.dt, dt6 = P.dt / 6.0;
+    double u, v;
+    const double V1x = vn.x, V1y = vn.y;
+    vel64<CUBIC, LANES>(rec0, tile, T, P, scheme, x.x, x.y, W.wa[0], W.wb[0], W.smode[0], u, v);
+    const double A1x = (u - V1x) * is, A1y = (v - V1y) * is;
+    const double V2x = vn.x + hdt * A1x, V2y = vn.y + hdt * A1y;
+    vel64<CUBIC, LANES>(rec0, tile, T, P, scheme, x.x + hdt * V1x, x.y + hdt * V1y, W.wa[1],
+                        W.wb[1], W.smode[1], u, v);
+    const double A2x = (u - V2x) * is, A2y = (v - V2y) * is;
+    const double V3x = vn.x + hdt * A2x, V3y = vn.y + hdt * A2y;
+    vel64<CUBIC, LANES>(rec0, tile, T, P, scheme, x.x + hdt * V2x, x.y + hdt * V2y, W.wa[2],
+                        W.wb[2], W.smode[2], u, v);
+    const double A3x = (u - V3x) * is, A3y = (v - V3y) * is;
+    const double V4x = vn.x + dt * A3x, V4y = vn.y + dt * A3y;
+    vel64<CUBIC, LANES>(rec0, tile, T, P, scheme, x.x + dt * V3x, x.y + dt * V3y, W.wa[3], W.wb[3],
+                        W.smode[3], u, v);
+    const double A4x = (u - V4x) * is, A4y = (v - V4y) * is;
+    ddx = dt6 * (V1x + 2.0 * V2x + 2.0 * V3x + V4x);
+    ddy = dt6 * (V1y + 2.0 * V2y + 2.0 * V3y + V4y);
+    vn = make_double2(vn.x + dt6 * (A1x + 2.0 * A2x + 2.0 * A3x + A4x),
+                      vn.y + dt6 * (A1y + 2.0 * A2y + 2.0 * A3y + A4y));
 }
 
 }  // namespace lpt

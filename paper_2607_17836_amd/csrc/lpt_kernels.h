@@ -48,6 +48,23 @@ constexpr int kTileWaste = 8;
 // Which time levels a stage needs: weights (1, 0), (0, 1), or a blend.
 enum SlotMode : int32_t { kSlot0 = 0, kSlot1 = 1, kBlend = 2 };
 
+// Temporal interpolation of one step.
+struct StageWeights {
+    double wa[4], wb[4];   // weights of slot 0 / slot 1 per RK4 stage
+    int32_t smode[4];      // SlotMode per RK4 stage
+    float waf[4], wbf[4];  // binary32 copies, rounded once on the host
+    int32_t ends_one;      // stages 1 and 4 read one level each: h0 and h3
+    int32_t h0, h3;
+    int32_t pad_;
+};
+
+// Consecutive steps taken by one launch (launch_small64 / launch_small32).
+constexpr int kMaxRun = 16;
+struct StepRun {
+    int32_t nsteps, pad_;
+    StageWeights w[kMaxRun];
+};
+
 struct StepParams {
     int32_t n;             // grid points per side
     int32_t pitch;         // n + 3 (padded row length)
@@ -57,13 +74,9 @@ struct StepParams {
     int32_t compat_edge;   // bicubic reverts to bilinear near the grid edge
     double L, h, invh;     // domain side, spacing, n/L
     double dt;
-    double wa[4], wb[4];   // temporal weights of slot 0 / slot 1 per RK4 stage
-    int32_t smode[4];      // SlotMode per RK4 stage
+    StageWeights w;        // temporal weights of the step's RK4 stages
     // binary32 copies for the FP32-split kernel, rounded once on the host
     float dtf, hdtf, dt6f; // dt, dt/2, dt/6
-    float waf[4], wbf[4];
-    int32_t ends_one;      // stages 1 and 4 read one level each: h0 and h3
-    int32_t h0, h3;
     int32_t persistent;    // grid sized to residency; workgroups loop over blocks
     int32_t tile_cap;      // LDS tile capacity in node records (0: no tile)
     float halo_scale;      // tile halo = halo_scale x the largest-speed displacement
@@ -158,6 +171,17 @@ hipError_t launch_step32(const StepParams &P, const State32 &S, const State32 &D
                          const uint32_t *perm, const float4 *rec, double *partials,
                          DevClock *clock, bool stats, int schemes, bool inertial, int block,
                          int grid, hipStream_t st);
+
+// The R.nsteps steps of one launch over every species, for small populations
+// (see step.hip): S, D and perm as above, with the statistics of the last step.
+hipError_t launch_small64(const StepParams &P, const StepRun &R, const State64 &S,
+                          const State64 &D, const uint32_t *perm, const Rec64 *rec,
+                          double *partials, DevClock *clock, bool stats, bool cubic,
+                          bool inertial, int block, hipStream_t st);
+hipError_t launch_small32(const StepParams &P, const StepRun &R, const State32 &S,
+                          const State32 &D, const uint32_t *perm, const float4 *rec,
+                          double *partials, DevClock *clock, bool stats, bool cubic,
+                          bool inertial, int block, hipStream_t st);
 
 // Statistics record of every species from the per-wave partials of a step
 // kernel launched with `block` threads per block (two fixed-order merge

@@ -274,9 +274,9 @@ StepParams make_params(const lpt_ctx *c)
     P.pitch = (int32_t)padded_pitch(c->n);
     P.mask = is_pow2(c->n) ? c->n - 1 : -1;
     for (int q = 0; q < 4; ++q) {
-        P.wa[q] = 1.0;
-        P.wb[q] = 0.0;
-        P.smode[q] = kSlot0;
+        P.w.wa[q] = 1.0;
+        P.w.wb[q] = 0.0;
+        P.w.smode[q] = kSlot0;
     }
     P.nspecies = (int32_t)c->sp.size();
     P.tile_cap = c->tile_cap;
@@ -1000,18 +1000,41 @@ lpt_status grow_records(lpt_ctx *c, int64_t nsteps, int32_t stats_every)
 
 // Temporal weights of the step about to be taken (global number c->steps,
 // starting at c->t).
-void step_weights(const lpt_ctx *c, double dt, StepParams &P)
+void step_weights(const lpt_ctx *c, double dt, StageWeights &W)
 {
     const double stage_c[4] = {0.0, 0.5, 0.5, 1.0};
     for (int q = 0; q < 4; ++q) {
-        weights_at(c, c->steps, c->t, c->t + stage_c[q] * dt, dt, P.wa[q], P.wb[q]);
-        P.smode[q] = slot_mode(P.wa[q], P.wb[q]);
-        P.waf[q] = (float)P.wa[q];
-        P.wbf[q] = (float)P.wb[q];
+        weights_at(c, c->steps, c->t, c->t + stage_c[q] * dt, dt, W.wa[q], W.wb[q]);
+        W.smode[q] = slot_mode(W.wa[q], W.wb[q]);
+        W.waf[q] = (float)W.wa[q];
+        W.wbf[q] = (float)W.wb[q];
     }
-    P.ends_one = P.smode[0] != kBlend && P.smode[3] != kBlend;
-    P.h0 = P.smode[0] == kSlot1 ? 1 : 0;
-    P.h3 = P.smode[3] == kSlot1 ? 1 : 0;
+    W.ends_one = W.smode[0] != kBlend && W.smode[3] != kBlend;
+    W.h0 = W.smode[0] == kSlot1 ? 1 : 0;
+    W.h3 = W.smode[3] == kSlot1 ? 1 : 0;
+}
+
+// Whether the step launches of this context take the small-population kernels,
+// which run several steps each.  The lines are where a launch of one step
+// breaks even with the tiled kernels (us a step, tiled / small at one step a
+// launch / small at 16, tracers and inertial particles mixed):
+//   bilinear FP64: n = 1024, 2^16 particles 14.1 / 12.2 / 8.8, 2^17 16.5 /
+//     17.1 / 12.5, 2^18 22.4 / 30.9 / 24.0; n = 128, 2^17 9.0 / 8.3 / 5.4;
+//   bilinear FP32: n = 1024, 2^18 14.6 / 14.0 / 9.5, 2^19 18.3 / 18.6 / 13.3;
+//   bicubic FP64: n = 128, 2^15 13.1 / 9.7 / 6.1, 2^16 12.7 / 13.7 / 9.7;
+//     n = 1024, 2^16 28.0 / 26.6 / 22.0, 2^18 56.4 / 45.9 / 36.8, 2^19 71.0 /
+//     76.2 / 64.7;
+//   bicubic FP32: n = 128, 2^15 8.2 / 7.2 / 3.9, 2^16 8.1 / 9.6 / 6.0;
+//     n = 1024, 2^17 19.1 / 18.1 / 13.6, 2^18 25.2 / 29.4 / 23.0.
+// At 2^12 particles a step takes 7.2 -> 2.8 us (bilinear FP64, 16 a launch)
+// and 14.0 -> 4.1 us (bicubic).  The bicubic line rises where the particles
+// are too sparse (under one in four cells) for a block's tile to be shared.
+bool small_population(const lpt_ctx *c)
+{
+    const bool fp64 = c->precision == LPT_FP64;
+    if (!c->has_cubic) return c->np <= (fp64 ? 1 << 17 : 1 << 18);
+    const bool sparse = 4 * c->np <= (int64_t)c->n * c->n;
+    return c->np <= (!sparse ? 1 << 15 : fp64 ? 1 << 18 : 1 << 17);
 }
 
 void set_dt(StepParams &P, double dt)
@@ -1030,7 +1053,9 @@ lpt_status run_steps(lpt_ctx *c, int64_t nsteps, double dt, int32_t stats_every,
 {
     StepParams P = make_params(c);
     set_dt(P, dt);
-    for (int64_t k = 0; k < nsteps; ++k) {
+    StepRun R{};
+    const bool small = small_population(c);
+    for (int64_t k = 0; k < nsteps;) {
         // the step right after a re-sort applies its permutation itself
         const uint32_t *perm = nullptr;
         if (!ckpt && c->sort_interval > 0 && c->steps % c->sort_interval == 0) {
@@ -1063,25 +1088,54 @@ lpt_status run_steps(lpt_ctx *c, int64_t nsteps, double dt, int32_t stats_every,
                                       (size_t)c->np * sizeof(double2), hipMemcpyDeviceToDevice,
                                       c->stream));
         }
-        step_weights(c, dt, P);
-        if (ckpt) {
-            StepWeights w;
-            for (int q = 0; q < 4; ++q) {
-                w.wa[q] = P.wa[q];
-                w.wb[q] = P.wb[q];
-            }
-            c->ck_w.push_back(w);
+        // the steps of this launch: one, or, for a small population, as many
+        // as follow without a record, a re-sort or a checkpoint in between
+        // (one where every launch is timed)
+        int64_t m = 1;
+        if (small && !c->time_kernels) {
+            m = std::min<int64_t>(kMaxRun, nsteps - k);
+            if (!ckpt && c->sort_interval > 0)
+                m = std::min<int64_t>(m, c->sort_interval - c->steps % c->sort_interval);
+            if (stats_every > 0) m = std::min<int64_t>(m, stats_every - c->steps % stats_every);
+            if (ckpt) m = std::min<int64_t>(m, c->ck_every - k % c->ck_every);
         }
-        const bool rec = stats_every > 0 && (c->steps + 1) % stats_every == 0;
-        if (!launch) {
-            c->nrec += rec ? 1 : 0;
+        R.nsteps = (int32_t)m;
+        for (int64_t j = 0; j < m; ++j) {
+            StageWeights &W = R.w[j];
+            step_weights(c, dt, W);
+            if (ckpt) {
+                StepWeights w;
+                for (int q = 0; q < 4; ++q) {
+                    w.wa[q] = W.wa[q];
+                    w.wb[q] = W.wb[q];
+                }
+                c->ck_w.push_back(w);
+            }
             c->t += dt;
             c->steps += 1;
+        }
+        k += m;
+        const bool rec = stats_every > 0 && c->steps % stats_every == 0;
+        if (!launch) {
+            c->nrec += rec ? 1 : 0;
             continue;
         }
+        P.w = R.w[0];
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (c->time_kernels) HIP_TRY(c, mark(c, e0));
-        if (c->precision == LPT_FP64) {
+        if (small) {
+            if (c->precision == LPT_FP64)
+                HIP_TRY(c, launch_small64(P, R, c->s64[c->cur], c->s64[perm ? 1 - c->cur : c->cur],
+                                          perm, static_cast<const Rec64 *>(c->rec), c->partials,
+                                          c->clock, rec, c->has_cubic, c->has_inertial, c->block,
+                                          c->stream));
+            else
+                HIP_TRY(c, launch_small32(P, R, c->s32[c->cur], c->s32[perm ? 1 - c->cur : c->cur],
+                                          perm, static_cast<const float4 *>(c->rec), c->partials,
+                                          c->clock, rec, c->has_cubic, c->has_inertial, c->block,
+                                          c->stream));
+            if (perm) c->cur = 1 - c->cur;
+        } else if (c->precision == LPT_FP64) {
             HIP_TRY(c, launch_step64(P, c->s64[c->cur], c->s64[perm ? 1 - c->cur : c->cur], perm,
                                      static_cast<const Rec64 *>(c->rec), c->partials, c->clock,
                                      rec, c->has_cubic, c->has_inertial, c->block,
@@ -1128,8 +1182,6 @@ lpt_status run_steps(lpt_ctx *c, int64_t nsteps, double dt, int32_t stats_every,
             }
             c->nrec += 1;
         }
-        c->t += dt;
-        c->steps += 1;
     }
     return LPT_OK;
 }
@@ -1359,9 +1411,9 @@ lpt_status reverse_sweep(lpt_ctx *c, int nl, double2 *&lam, double2 *&lam_spare,
         for (int64_t s = 1; s < len && e == hipSuccess; ++s) {
             const StepWeights &w = c->ck_w[(size_t)(k0 + s - 1)];
             for (int q = 0; q < 4; ++q) {
-                P.wa[q] = w.wa[q];
-                P.wb[q] = w.wb[q];
-                P.smode[q] = slot_mode(w.wa[q], w.wb[q]);
+                P.w.wa[q] = w.wa[q];
+                P.w.wb[q] = w.wb[q];
+                P.w.smode[q] = slot_mode(w.wa[q], w.wb[q]);
             }
             e = launch_recompute64(P, rec, tape + (s - 1) * np, tape + s * np, c->has_cubic,
                                    c->block, c->stream);
@@ -1369,9 +1421,9 @@ lpt_status reverse_sweep(lpt_ctx *c, int nl, double2 *&lam, double2 *&lam_spare,
         for (int64_t s = len - 1; s >= 0 && e == hipSuccess; --s) {
             const StepWeights &w = c->ck_w[(size_t)(k0 + s)];
             for (int q = 0; q < 4; ++q) {
-                P.wa[q] = w.wa[q];
-                P.wb[q] = w.wb[q];
-                P.smode[q] = slot_mode(w.wa[q], w.wb[q]);
+                P.w.wa[q] = w.wa[q];
+                P.w.wb[q] = w.wb[q];
+                P.w.smode[q] = slot_mode(w.wa[q], w.wb[q]);
             }
             e = launch_adjoint64(P, rec, tape + s * np, lam, nl, gU, det, c->has_cubic,
                                  c->block, c->stream);
