@@ -115,23 +115,26 @@ __device__ __forceinline__ void jacobian_nodes(const Nodes &N, const StepParams 
                                                int smode, double J[4])
 {
     double ux = 0.0, uy = 0.0, vx = 0.0, vy = 0.0;
+    with_smode(smode, [&](auto mode) {
+        constexpr int SM = decltype(mode)::value;
 #pragma unroll
-    for (int b = 0; b < K; ++b) {
-        double rux = 0.0, rvx = 0.0, ru = 0.0, rv = 0.0;
+        for (int b = 0; b < K; ++b) {
+            double rux = 0.0, rvx = 0.0, ru = 0.0, rv = 0.0;
 #pragma unroll
-        for (int a = 0; a < K; ++a) {
-            double u, v;
-            N.get(a, b, smode, wa, wb, u, v);
-            rux += s.dx[a] * u;
-            rvx += s.dx[a] * v;
-            ru += s.wx[a] * u;
-            rv += s.wx[a] * v;
+            for (int a = 0; a < K; ++a) {
+                double u, v;
+                N.template get<SM>(a, b, wa, wb, u, v);
+                rux += s.dx[a] * u;
+                rvx += s.dx[a] * v;
+                ru += s.wx[a] * u;
+                rv += s.wx[a] * v;
+            }
+            ux += s.wy[b] * rux;
+            vx += s.wy[b] * rvx;
+            uy += s.dy[b] * ru;
+            vy += s.dy[b] * rv;
         }
-        ux += s.wy[b] * rux;
-        vx += s.wy[b] * rvx;
-        uy += s.dy[b] * ru;
-        vy += s.dy[b] * rv;
-    }
+    });
     J[0] = ux * P.invh;
     J[1] = uy * P.invh;
     J[2] = vx * P.invh;

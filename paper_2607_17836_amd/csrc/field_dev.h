@@ -8,6 +8,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace lpt {
 
 constexpr int kMaxBlock = 512;
@@ -583,41 +585,48 @@ __device__ __forceinline__ void stencil_reach(int scheme, int &lo, int &hi)
 // FP64 path (physical units)
 // ===========================================================================
 // Time-blended (u, v) of one node from its two levels (level 0 at q0, level 1
-// at q1; only the ones smode needs are read).
-__device__ __forceinline__ void blend64(const double2 *q0, const double2 *q1, int smode,
-                                        double wa, double wb, double &u, double &v)
+// at q1; only the ones the stage's SlotMode SM needs are read).  SM is a
+// compile-time value all the way down from the stencil: chosen per node, the
+// (uniform) branch kept every node's load behind the use of the one before.
+// The fused product of the blend is spelt out, so that every kernel forms it
+// alike.
+template <int SM>
+__device__ __forceinline__ void blend64(const double2 *q0, const double2 *q1, double wa, double wb,
+                                        double &u, double &v)
 {
-    if (smode == kSlot0) {
-        const double2 a = *q0;
+    const double2 a = SM == kSlot1 ? *q1 : *q0;
+    if constexpr (SM == kBlend) {
+        const double2 b = *q1;
+        u = fma(wa, a.x, wb * b.x);
+        v = fma(wa, a.y, wb * b.y);
+    } else {
         u = a.x;
         v = a.y;
-    } else if (smode == kSlot1) {
-        const double2 b = *q1;
-        u = b.x;
-        v = b.y;
-    } else {
-        const double2 a = *q0, b = *q1;
-        u = wa * a.x + wb * b.x;
-        v = wa * a.y + wb * b.y;
     }
 }
 
-// Time-blended (u, v) of one node record.
-__device__ __forceinline__ void node64(const Rec64 *r, int smode, double wa, double wb, double &u,
-                                       double &v)
+// f(mode) with the stage's SlotMode as a compile-time constant.
+template <typename F>
+__device__ __forceinline__ void with_smode(int smode, F f)
 {
-    const double2 *q = reinterpret_cast<const double2 *>(r);
-    blend64(q, q + 1, smode, wa, wb, u, v);
+    if (smode == kSlot0)
+        f(std::integral_constant<int, kSlot0>{});
+    else if (smode == kSlot1)
+        f(std::integral_constant<int, kSlot1>{});
+    else
+        f(std::integral_constant<int, kBlend>{});
 }
 
 // Stencil nodes in global memory: whole records, node (a, b) at p + b pitch + a.
 struct RecNodes64 {
     const Rec64 *p;
     int pitch;
-    __device__ __forceinline__ void get(int a, int b, int smode, double wa, double wb, double &u,
+    template <int SM>
+    __device__ __forceinline__ void get(int a, int b, double wa, double wb, double &u,
                                         double &v) const
     {
-        node64(p + (b * pitch + a), smode, wa, wb, u, v);
+        const double2 *q = reinterpret_cast<const double2 *>(p + (b * pitch + a));
+        blend64<SM>(q, q + 1, wa, wb, u, v);
     }
 };
 
@@ -626,11 +635,12 @@ struct RecNodes64 {
 struct TileNodes64 {
     const double2 *p;
     int pitch, area;
-    __device__ __forceinline__ void get(int a, int b, int smode, double wa, double wb, double &u,
+    template <int SM>
+    __device__ __forceinline__ void get(int a, int b, double wa, double wb, double &u,
                                         double &v) const
     {
         const double2 *q = p + (b * pitch + a);
-        blend64(q, q + area, smode, wa, wb, u, v);
+        blend64<SM>(q, q + area, wa, wb, u, v);
     }
 };
 
@@ -639,15 +649,18 @@ template <typename Nodes>
 __device__ __forceinline__ void bil64(const Nodes &N, double xi, double eta, int smode,
                                       double wa, double wb, double &u, double &v)
 {
-    double u00, v00, u10, v10, u01, v01, u11, v11;
-    N.get(0, 0, smode, wa, wb, u00, v00);
-    N.get(1, 0, smode, wa, wb, u10, v10);
-    N.get(0, 1, smode, wa, wb, u01, v01);
-    N.get(1, 1, smode, wa, wb, u11, v11);
-    double w00, w10, w01, w11;
-    bilinear_weights(xi, eta, w00, w10, w01, w11);
-    u = w00 * u00 + w10 * u10 + w01 * u01 + w11 * u11;
-    v = w00 * v00 + w10 * v10 + w01 * v01 + w11 * v11;
+    with_smode(smode, [&](auto mode) {
+        constexpr int SM = decltype(mode)::value;
+        double u00, v00, u10, v10, u01, v01, u11, v11;
+        N.template get<SM>(0, 0, wa, wb, u00, v00);
+        N.template get<SM>(1, 0, wa, wb, u10, v10);
+        N.template get<SM>(0, 1, wa, wb, u01, v01);
+        N.template get<SM>(1, 1, wa, wb, u11, v11);
+        double w00, w10, w01, w11;
+        bilinear_weights(xi, eta, w00, w10, w01, w11);
+        u = w00 * u00 + w10 * u10 + w01 * u01 + w11 * u11;
+        v = w00 * v00 + w10 * v10 + w01 * v01 + w11 * v11;
+    });
 }
 
 // eqs. cr_interp / bspline_interp on the 4x4 nodes of N (node (0, 0) is grid
@@ -656,22 +669,25 @@ template <typename Nodes>
 __device__ __forceinline__ void cub64(const Nodes &N, const double wx[4], const double wy[4],
                                       int smode, double wa, double wb, double &u, double &v)
 {
-    double au = 0.0, av = 0.0;
+    with_smode(smode, [&](auto mode) {
+        constexpr int SM = decltype(mode)::value;
+        double au = 0.0, av = 0.0;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        double ru = 0.0, rv = 0.0;
+        for (int b = 0; b < 4; ++b) {
+            double ru = 0.0, rv = 0.0;
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            double nu, nv;
-            N.get(a, b, smode, wa, wb, nu, nv);
-            ru += wx[a] * nu;
-            rv += wx[a] * nv;
+            for (int a = 0; a < 4; ++a) {
+                double nu, nv;
+                N.template get<SM>(a, b, wa, wb, nu, nv);
+                ru += wx[a] * nu;
+                rv += wx[a] * nv;
+            }
+            au += wy[b] * ru;
+            av += wy[b] * rv;
         }
-        au += wy[b] * ru;
-        av += wy[b] * rv;
-    }
-    u = au;
-    v = av;
+        u = au;
+        v = av;
+    });
 }
 
 // cub64 by a group of four lanes, one row of the stencil each: the same sums in
@@ -682,13 +698,16 @@ __device__ __forceinline__ void cub64_quad(const Nodes &N, const double wx[4], c
 {
     const int b = (int)threadIdx.x & 3;
     double ru = 0.0, rv = 0.0;
+    with_smode(smode, [&](auto mode) {
+        constexpr int SM = decltype(mode)::value;
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        double nu, nv;
-        N.get(a, b, smode, wa, wb, nu, nv);
-        ru += wx[a] * nu;
-        rv += wx[a] * nv;
-    }
+        for (int a = 0; a < 4; ++a) {
+            double nu, nv;
+            N.template get<SM>(a, b, wa, wb, nu, nv);
+            ru += wx[a] * nu;
+            rv += wx[a] * nv;
+        }
+    });
     u = quad_rows(wy, ru);
     v = quad_rows(wy, rv);
 }

@@ -95,11 +95,19 @@ __device__ __forceinline__ void step64_block(const StepParams &P, const State64 
     }
 }
 
+// Bound by the latency of the stages' gathers, so by the waves that stay
+// resident: registers are bounded to six waves per SIMD for bilinear tracers
+// (76 registers; an 800-record tile leaves room for six blocks) and to four
+// otherwise (121-127; unbounded 133 and three waves).  With each stage's loads
+// in flight together (see blend64): 1024^2 Catmull-Rom, 2^20 tracers + 2^20
+// inertial particles 136 -> 106 us a step; 2048^2, 2^20 bilinear tracers 58.9
+// -> 51.4 us; 4096^2, 2^24 bilinear tracers 421 -> 394 us with the shipped
+// 800-record tile, 479 -> 447 us with the default.
 template <bool CUBIC, bool INERTIAL, bool STATS>
-__global__ __launch_bounds__(kMaxBlock) void step64_kernel(StepParams P, State64 S,
-                                                           const Rec64 *__restrict__ rec,
-                                                           double *__restrict__ partials,
-                                                           DevClock *clock)
+__global__ __launch_bounds__(kMaxBlock)
+__attribute__((amdgpu_waves_per_eu(CUBIC || INERTIAL ? 4 : 6)))
+void step64_kernel(StepParams P, State64 S, const Rec64 *__restrict__ rec,
+                   double *__restrict__ partials, DevClock *clock)
 {
     BlockWalk w = block_walk(P, 0, P.total_blocks);
     for (int lb = 0; block_next(w, lb);)
@@ -108,11 +116,11 @@ __global__ __launch_bounds__(kMaxBlock) void step64_kernel(StepParams P, State64
 
 // The FP64 step that follows a re-sort: reads S through perm, writes D.
 template <bool CUBIC, bool INERTIAL, bool STATS>
-__global__ __launch_bounds__(kMaxBlock) void step64_perm_kernel(StepParams P, State64 S,
-                                                                State64 D, const uint32_t *perm,
-                                                                const Rec64 *__restrict__ rec,
-                                                                double *__restrict__ partials,
-                                                                DevClock *clock)
+__global__ __launch_bounds__(kMaxBlock)
+__attribute__((amdgpu_waves_per_eu(CUBIC || INERTIAL ? 4 : 6)))
+void step64_perm_kernel(StepParams P, State64 S, State64 D, const uint32_t *perm,
+                        const Rec64 *__restrict__ rec, double *__restrict__ partials,
+                        DevClock *clock)
 {
     BlockWalk w = block_walk(P, 0, P.total_blocks);
     for (int lb = 0; block_next(w, lb);)
