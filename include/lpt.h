@@ -85,8 +85,9 @@ typedef enum { LPT_TIME_BRACKET = 0, LPT_TIME_PINGPONG = 1 } lpt_time_mode;
 #define LPT_FLAG_TIME_KERNELS 0x2u /* record HIP events around every step-kernel
                                       launch and every re-sort, on the context
                                       stream (see lpt_get_timing); launches then
-                                      take one step each, where a small
-                                      population's would take several           */
+                                      take one step each, where they otherwise
+                                      take all steps of a call up to the next
+                                      record or re-sort (at most 16)            */
 #define LPT_FLAG_DETERMINISTIC_GRAD 0x4u /* lpt_adjoint sums the grid gradient
                                       exactly in fixed point (each contribution
                                       rounded once to a multiple of 2^-64, |entries|

@@ -120,10 +120,13 @@ __device__ __forceinline__ void jacobian_nodes(const Nodes &N, const StepParams 
 #pragma unroll
         for (int b = 0; b < K; ++b) {
             double rux = 0.0, rvx = 0.0, ru = 0.0, rv = 0.0;
+            typename Nodes::template Raw<SM> raw[K];
+#pragma unroll
+            for (int a = 0; a < K; ++a) raw[a] = N.template load<SM>(a, b);
 #pragma unroll
             for (int a = 0; a < K; ++a) {
                 double u, v;
-                N.template get<SM>(a, b, wa, wb, u, v);
+                raw[a].blend(wa, wb, u, v);
                 rux += s.dx[a] * u;
                 rvx += s.dx[a] * v;
                 ru += s.wx[a] * u;

@@ -584,26 +584,31 @@ __device__ __forceinline__ void stencil_reach(int scheme, int &lo, int &hi)
 // ===========================================================================
 // FP64 path (physical units)
 // ===========================================================================
-// Time-blended (u, v) of one node from its two levels (level 0 at q0, level 1
-// at q1; only the ones the stage's SlotMode SM needs are read).  SM is a
-// compile-time value all the way down from the stencil: chosen per node, the
-// (uniform) branch kept every node's load behind the use of the one before.
-// The fused product of the blend is spelt out, so that every kernel forms it
-// alike.
+// One node's levels as loaded (level 0 at q0, level 1 at q1; only the ones the
+// stage's SlotMode SM needs) and their time blend.  SM is a compile-time value
+// all the way down from the stencil: chosen per node, the (uniform) branch
+// kept every node's load behind the use of the one before.  The fused product
+// of the blend is spelt out, so that every kernel forms it alike.
 template <int SM>
-__device__ __forceinline__ void blend64(const double2 *q0, const double2 *q1, double wa, double wb,
-                                        double &u, double &v)
-{
-    const double2 a = SM == kSlot1 ? *q1 : *q0;
-    if constexpr (SM == kBlend) {
-        const double2 b = *q1;
-        u = fma(wa, a.x, wb * b.x);
-        v = fma(wa, a.y, wb * b.y);
-    } else {
-        u = a.x;
-        v = a.y;
+struct NodeRaw64 {
+    double2 a, b;
+    __device__ __forceinline__ NodeRaw64() {}
+    __device__ __forceinline__ NodeRaw64(const double2 *q0, const double2 *q1)
+    {
+        a = SM == kSlot1 ? *q1 : *q0;
+        if constexpr (SM == kBlend) b = *q1;
     }
-}
+    __device__ __forceinline__ void blend(double wa, double wb, double &u, double &v) const
+    {
+        if constexpr (SM == kBlend) {
+            u = fma(wa, a.x, wb * b.x);
+            v = fma(wa, a.y, wb * b.y);
+        } else {
+            u = a.x;
+            v = a.y;
+        }
+    }
+};
 
 // f(mode) with the stage's SlotMode as a compile-time constant.
 template <typename F>
@@ -619,28 +624,30 @@ __device__ __forceinline__ void with_smode(int smode, F f)
 
 // Stencil nodes in global memory: whole records, node (a, b) at p + b pitch + a.
 struct RecNodes64 {
+    template <int SM>
+    using Raw = NodeRaw64<SM>;
     const Rec64 *p;
     int pitch;
     template <int SM>
-    __device__ __forceinline__ void get(int a, int b, double wa, double wb, double &u,
-                                        double &v) const
+    __device__ __forceinline__ Raw<SM> load(int a, int b) const
     {
         const double2 *q = reinterpret_cast<const double2 *>(p + (b * pitch + a));
-        blend64<SM>(q, q + 1, wa, wb, u, v);
+        return Raw<SM>(q, q + 1);
     }
 };
 
 // Stencil nodes in the LDS tile: two planes of (u, v), level 0 then level 1,
 // `area` entries apart; node (a, b) at entry b pitch + a from p.
 struct TileNodes64 {
+    template <int SM>
+    using Raw = NodeRaw64<SM>;
     const double2 *p;
     int pitch, area;
     template <int SM>
-    __device__ __forceinline__ void get(int a, int b, double wa, double wb, double &u,
-                                        double &v) const
+    __device__ __forceinline__ Raw<SM> load(int a, int b) const
     {
         const double2 *q = p + (b * pitch + a);
-        blend64<SM>(q, q + area, wa, wb, u, v);
+        return Raw<SM>(q, q + area);
     }
 };
 
@@ -651,11 +658,13 @@ __device__ __forceinline__ void bil64(const Nodes &N, double xi, double eta, int
 {
     with_smode(smode, [&](auto mode) {
         constexpr int SM = decltype(mode)::value;
+        const auto r00 = N.template load<SM>(0, 0), r10 = N.template load<SM>(1, 0);
+        const auto r01 = N.template load<SM>(0, 1), r11 = N.template load<SM>(1, 1);
         double u00, v00, u10, v10, u01, v01, u11, v11;
-        N.template get<SM>(0, 0, wa, wb, u00, v00);
-        N.template get<SM>(1, 0, wa, wb, u10, v10);
-        N.template get<SM>(0, 1, wa, wb, u01, v01);
-        N.template get<SM>(1, 1, wa, wb, u11, v11);
+        r00.blend(wa, wb, u00, v00);
+        r10.blend(wa, wb, u10, v10);
+        r01.blend(wa, wb, u01, v01);
+        r11.blend(wa, wb, u11, v11);
         double w00, w10, w01, w11;
         bilinear_weights(xi, eta, w00, w10, w01, w11);
         u = w00 * u00 + w10 * u10 + w01 * u01 + w11 * u11;
@@ -671,19 +680,29 @@ __device__ __forceinline__ void cub64(const Nodes &N, const double wx[4], const 
 {
     with_smode(smode, [&](auto mode) {
         constexpr int SM = decltype(mode)::value;
+        // the loads of kRows rows (eight of 16 bytes) before their first use
+        constexpr int kRows = SM == kBlend ? 1 : 2;
         double au = 0.0, av = 0.0;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            double ru = 0.0, rv = 0.0;
+        for (int b0 = 0; b0 < 4; b0 += kRows) {
+            typename Nodes::template Raw<SM> raw[kRows][4];
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                double nu, nv;
-                N.template get<SM>(a, b, wa, wb, nu, nv);
-                ru += wx[a] * nu;
-                rv += wx[a] * nv;
+            for (int b = 0; b < kRows; ++b)
+#pragma unroll
+                for (int a = 0; a < 4; ++a) raw[b][a] = N.template load<SM>(a, b0 + b);
+#pragma unroll
+            for (int b = 0; b < kRows; ++b) {
+                double ru = 0.0, rv = 0.0;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    double nu, nv;
+                    raw[b][a].blend(wa, wb, nu, nv);
+                    ru += wx[a] * nu;
+                    rv += wx[a] * nv;
+                }
+                au += wy[b0 + b] * ru;
+                av += wy[b0 + b] * rv;
             }
-            au += wy[b] * ru;
-            av += wy[b] * rv;
         }
         u = au;
         v = av;
@@ -700,10 +719,13 @@ __device__ __forceinline__ void cub64_quad(const Nodes &N, const double wx[4], c
     double ru = 0.0, rv = 0.0;
     with_smode(smode, [&](auto mode) {
         constexpr int SM = decltype(mode)::value;
+        typename Nodes::template Raw<SM> raw[4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) raw[a] = N.template load<SM>(a, b);
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
             double nu, nv;
-            N.template get<SM>(a, b, wa, wb, nu, nv);
+            raw[a].blend(wa, wb, nu, nv);
             ru += wx[a] * nu;
             rv += wx[a] * nv;
         }

@@ -58,7 +58,7 @@ struct StageWeights {
     int32_t pad_;
 };
 
-// Consecutive steps taken by one launch (launch_small64 / launch_small32).
+// Consecutive steps taken by one launch.
 constexpr int kMaxRun = 16;
 struct StepRun {
     int32_t nsteps, pad_;
@@ -156,21 +156,23 @@ hipError_t launch_pack(void *rec, bool fp64, int slot, const double *u, const do
 hipError_t launch_pack_psi(void *rec, bool fp64, int slot, const double *psi, int n, double h,
                            double scale, double vscale, float *umax, hipStream_t st);
 
-// The step works in place on S; with perm (the permutation of a re-sort, dst
-// slot -> src slot) it reads S through perm and writes D, a different buffer,
-// so that it also applies the permutation (id included).
-hipError_t launch_step64(const StepParams &P, const State64 &S, const State64 &D,
-                         const uint32_t *perm, const Rec64 *rec, double *partials,
-                         DevClock *clock, bool stats, bool cubic, bool inertial, int block,
-                         int grid, hipStream_t st);
+// R.nsteps steps in one launch (P.w holds the weights of the first), with the
+// statistics of the last.  They work in place (D = S), or, with perm (the
+// permutation of a re-sort, dst slot -> src slot), read S through perm and
+// write D, a different buffer, so that they also apply the permutation (id
+// included).
+hipError_t launch_step64(const StepParams &P, const StepRun &R, const State64 &S,
+                         const State64 &D, const uint32_t *perm, const Rec64 *rec,
+                         double *partials, DevClock *clock, bool stats, bool cubic,
+                         bool inertial, int block, int grid, hipStream_t st);
 // One launch over the logical blocks [P.block_base, P.block_base +
 // P.launch_blocks) (= grid) of one species, whose scheme is `schemes`, or,
 // with P.order set and schemes = kAnyScheme (or the one scheme they share),
-// a fused launch over every species.  S, D and perm as for launch_step64.
-hipError_t launch_step32(const StepParams &P, const State32 &S, const State32 &D,
-                         const uint32_t *perm, const float4 *rec, double *partials,
-                         DevClock *clock, bool stats, int schemes, bool inertial, int block,
-                         int grid, hipStream_t st);
+// a fused launch over every species.  R, S, D and perm as for launch_step64.
+hipError_t launch_step32(const StepParams &P, const StepRun &R, const State32 &S,
+                         const State32 &D, const uint32_t *perm, const float4 *rec,
+                         double *partials, DevClock *clock, bool stats, int schemes,
+                         bool inertial, int block, int grid, hipStream_t st);
 
 // The R.nsteps steps of one launch over every species, for small populations
 // (see step.hip): S, D and perm as above, with the statistics of the last step.

@@ -1014,27 +1014,29 @@ void step_weights(const lpt_ctx *c, double dt, StageWeights &W)
     W.h3 = W.smode[3] == kSlot1 ? 1 : 0;
 }
 
-// Whether the step launches of this context take the small-population kernels,
-// which run several steps each.  The lines are where a launch of one step
-// breaks even with the tiled kernels (us a step, tiled / small at one step a
-// launch / small at 16, tracers and inertial particles mixed):
-//   bilinear FP64: n = 1024, 2^16 particles 14.1 / 12.2 / 8.8, 2^17 16.5 /
-//     17.1 / 12.5, 2^18 22.4 / 30.9 / 24.0; n = 128, 2^17 9.0 / 8.3 / 5.4;
-//   bilinear FP32: n = 1024, 2^18 14.6 / 14.0 / 9.5, 2^19 18.3 / 18.6 / 13.3;
-//   bicubic FP64: n = 128, 2^15 13.1 / 9.7 / 6.1, 2^16 12.7 / 13.7 / 9.7;
-//     n = 1024, 2^16 28.0 / 26.6 / 22.0, 2^18 56.4 / 45.9 / 36.8, 2^19 71.0 /
-//     76.2 / 64.7;
-//   bicubic FP32: n = 128, 2^15 8.2 / 7.2 / 3.9, 2^16 8.1 / 9.6 / 6.0;
-//     n = 1024, 2^17 19.1 / 18.1 / 13.6, 2^18 25.2 / 29.4 / 23.0.
-// At 2^12 particles a step takes 7.2 -> 2.8 us (bilinear FP64, 16 a launch)
-// and 14.0 -> 4.1 us (bicubic).  The bicubic line rises where the particles
-// are too sparse (under one in four cells) for a block's tile to be shared.
+// Whether the step launches of this context take the small-population kernels
+// (no tile, a bicubic stencil over four lanes) rather than the tiled ones.  They
+// pay while the launch does not fill the chip, and where the particles are too
+// sparse for a block's tile to be shared.  Us a step, tiled / small, one step a
+// launch (and 16):
+//   bilinear FP64: n = 512, 2^18 particles 13.4 / 13.1 (9.8 / 9.6), 2^20 30.6 /
+//     31.3 (22.8 / 25.1); n = 4096, 2^20 126 / 104 (82 / 74), 2^22 200 / 229;
+//   bilinear FP32: n = 1024, 2^18 13.1 / 11.4 (9.1 / 8.0), 2^19 16.0 / 15.9;
+//     n = 4096, 2^20 59 / 61 (54 / 48), 2^21 71 / 98;
+//   bicubic FP64: n = 512, 2^16 15.5 / 14.6 (13.0 / 11.6), 2^17 17.9 / 23.3;
+//     n = 1024, 2^18 32 / 42; n = 4096, 2^20 258 / 188, 2^22 339 / 519;
+//   bicubic FP32: n = 512, 2^16 13.2 / 11.7, 2^17 14.3 / 17.4; n = 4096, 2^19
+//     102 / 64 (103 / 51), 2^20 109 / 108 (103 / 86), 2^21 129 / 185.
+// At 2^12 particles, n = 1024, a step took 10.2 (bilinear FP64) and 22.7 us
+// (bicubic FP64) in the tiled kernels: 5.1 and 6.5 us now, 2.2 and 3.3 us in
+// launches of 16.
 bool small_population(const lpt_ctx *c)
 {
-    const bool fp64 = c->precision == LPT_FP64;
-    if (!c->has_cubic) return c->np <= (fp64 ? 1 << 17 : 1 << 18);
-    const bool sparse = 4 * c->np <= (int64_t)c->n * c->n;
-    return c->np <= (!sparse ? 1 << 15 : fp64 ? 1 << 18 : 1 << 17);
+    const int64_t np = c->np, nn = (int64_t)c->n * c->n;
+    if (c->has_cubic)
+        return np <= 1 << 15 || (np <= 1 << 16 && 4 * np <= nn) || 16 * np <= nn;
+    if (np <= 1 << 18) return true;
+    return c->precision == LPT_FP64 ? 8 * np <= nn : np <= 1 << 20 && 16 * np <= nn;
 }
 
 void set_dt(StepParams &P, double dt)
@@ -1088,11 +1090,14 @@ lpt_status run_steps(lpt_ctx *c, int64_t nsteps, double dt, int32_t stats_every,
                                       (size_t)c->np * sizeof(double2), hipMemcpyDeviceToDevice,
                                       c->stream));
         }
-        // the steps of this launch: one, or, for a small population, as many
-        // as follow without a record, a re-sort or a checkpoint in between
-        // (one where every launch is timed)
+        // the steps of this launch: as many as follow without a record, a
+        // re-sort or a checkpoint in between (one where every launch is
+        // timed).  The particles then stay in registers between them, which
+        // takes their state's round trip through memory out: 2^24 FP32-split
+        // tracers on 4096^2, 199 us a step one by one, 151 in fours, 132 in
+        // sixteens.
         int64_t m = 1;
-        if (small && !c->time_kernels) {
+        if (!c->time_kernels) {
             m = std::min<int64_t>(kMaxRun, nsteps - k);
             if (!ckpt && c->sort_interval > 0)
                 m = std::min<int64_t>(m, c->sort_interval - c->steps % c->sort_interval);
@@ -1136,7 +1141,7 @@ lpt_status run_steps(lpt_ctx *c, int64_t nsteps, double dt, int32_t stats_every,
                                           c->stream));
             if (perm) c->cur = 1 - c->cur;
         } else if (c->precision == LPT_FP64) {
-            HIP_TRY(c, launch_step64(P, c->s64[c->cur], c->s64[perm ? 1 - c->cur : c->cur], perm,
+            HIP_TRY(c, launch_step64(P, R, c->s64[c->cur], c->s64[perm ? 1 - c->cur : c->cur], perm,
                                      static_cast<const Rec64 *>(c->rec), c->partials, c->clock,
                                      rec, c->has_cubic, c->has_inertial, c->block,
                                      P.total_blocks, c->stream));
@@ -1147,7 +1152,7 @@ lpt_status run_steps(lpt_ctx *c, int64_t nsteps, double dt, int32_t stats_every,
             int sch = P.sp[0].scheme;
             for (int s = 1; s < P.nspecies; ++s)
                 if (P.sp[s].scheme != sch) sch = kAnyScheme;
-            HIP_TRY(c, launch_step32(P, c->s32[c->cur], c->s32[perm ? 1 - c->cur : c->cur], perm,
+            HIP_TRY(c, launch_step32(P, R, c->s32[c->cur], c->s32[perm ? 1 - c->cur : c->cur], perm,
                                      static_cast<const float4 *>(c->rec), c->partials, c->clock,
                                      rec, sch, c->has_inertial, c->block, P.total_blocks,
                                      c->stream));
@@ -1161,7 +1166,7 @@ lpt_status run_steps(lpt_ctx *c, int64_t nsteps, double dt, int32_t stats_every,
                 StepParams Q = P;
                 Q.block_base = d.block_begin;
                 Q.launch_blocks = d.block_end - d.block_begin;
-                HIP_TRY(c, launch_step32(Q, c->s32[c->cur], c->s32[perm ? 1 - c->cur : c->cur],
+                HIP_TRY(c, launch_step32(Q, R, c->s32[c->cur], c->s32[perm ? 1 - c->cur : c->cur],
                                          perm, static_cast<const float4 *>(c->rec), c->partials,
                                          c->clock, rec, d.scheme, d.inertial != 0, c->block,
                                          Q.launch_blocks, c->stream));

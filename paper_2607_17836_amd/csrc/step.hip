@@ -21,12 +21,108 @@
 
 namespace lpt {
 
-// One logical block of the FP64 step: the state of slot p is read from S and
-// written to D, in place, or, on a step that follows a re-sort (GATHER), slot
-// p of D takes the particle of slot perm[p] of S, id included.
-template <bool CUBIC, bool INERTIAL, bool STATS, bool GATHER>
+// The device clock after `steps` steps, added as that many launches add them
+// (by one thread of the launch: the caller picks the block).
+__device__ __forceinline__ void advance_clock(const StepParams &P, int steps, DevClock *clock)
+{
+    if (threadIdx.x == 0) {
+        double t = clock->t;
+        for (int k = 0; k < steps; ++k) t += P.dt;
+        clock->t = t;
+        clock->step += steps;
+    }
+}
+
+// Field tile of one logical block for one FP64 step: the box of its particles'
+// cells around the anchor cell (ax, ay), with the halo and the stencil's reach.
+__device__ __forceinline__ Tile tile64(const StepParams &P, const SpeciesDev &sp, Rec64 *lds,
+                                       const Rec64 *__restrict__ rec0, double2 x, bool active,
+                                       int ax, int ay, int64_t base)
+{
+    const int n = P.n, mask = P.mask;
+    const int cx = cell_of_floor(floor(x.x * P.invh), n, mask);
+    const int cy = cell_of_floor(floor(x.y * P.invh), n, mask);
+    int lo, hi;
+    stencil_reach(sp.scheme, lo, hi);
+    const int H = step_halo(P, sp.scheme, (float)P.dt);
+    const int64_t left = sp.count - base;
+    return stage_tile<Rec64>(lds, rec0, P, active, cx, cy, ax, ay, lo + H, hi + H,
+                             (int)(left < (int64_t)blockDim.x ? left : blockDim.x));
+}
+
+// One logical block of the FP64 run kernel: R.nsteps steps of the block's
+// particles, which stay in registers, with a new tile for each.  Slot p of D
+// takes the particle of slot p of S (D = S: in place), or, on the steps that
+// follow a re-sort, of slot perm[p], id included.  The box of a step is taken
+// about the centre of the box before (any cell near the particles will do).
+template <bool CUBIC, bool INERTIAL, bool STATS>
+__device__ __forceinline__ void run64_block(const StepParams &P, const StepRun &R,
+                                            const State64 &S, const State64 &D,
+                                            const uint32_t *perm, const Rec64 *__restrict__ rec,
+                                            double *__restrict__ partials, DevClock *clock, int lb)
+{
+    Rec64 *lds = reinterpret_cast<Rec64 *>(lpt_dyn_lds);
+    const double2 *planes = reinterpret_cast<const double2 *>(lpt_dyn_lds);   // tile, two planes
+    const SpeciesDev &sp = P.sp[species_of(P, lb)];
+    const int64_t base = (int64_t)(lb - sp.block_begin) * blockDim.x;
+    const int64_t local = base + threadIdx.x;
+    const bool active = local < sp.count;
+    const int64_t p = sp.offset + local;
+    const Rec64 *rec0 = rec + P.pitch + 1;
+    const bool inert = INERTIAL && sp.inertial;
+
+    int64_t q = p;
+    double2 x = make_double2(0.0, 0.0), d = x, vn = x;
+    if (active) {
+        if (perm) q = perm[p];
+        x = S.pos[q];
+        d = S.disp[q];
+        if (inert) vn = S.vel[q];
+    }
+    int ax = 0, ay = 0;
+    if (P.tile_cap > 0) {
+        const int64_t a0 = sp.offset + base;
+        const double2 a = S.pos[perm ? (int64_t)perm[a0] : a0];
+        ax = cell_of_floor(floor(a.x * P.invh), P.n, P.mask);
+        ay = cell_of_floor(floor(a.y * P.invh), P.n, P.mask);
+    }
+    for (int k = 0; k < R.nsteps; ++k) {
+        const StageWeights &W = R.w[k];
+        Tile T = no_tile();
+        if (P.tile_cap > 0) {
+            T = tile64(P, sp, lds, rec0, x, active, ax, ay, base);
+            ax = wrap_cell(T.x0 + T.w / 2, P.n, P.mask);
+            ay = wrap_cell(T.y0 + T.h / 2, P.n, P.mask);
+        }
+        if (active) {
+            double ddx, ddy;
+            if (inert)
+                rk4_inertial64<CUBIC>(rec0, planes, T, P, W, sp.scheme, sp.inv_st, x, vn, ddx, ddy);
+            else
+                rk4_tracer64<CUBIC>(rec0, planes, T, P, W, sp.scheme, x, ddx, ddy);
+            x = make_double2(wrap_pos(x.x + ddx, P.L), wrap_pos(x.y + ddy, P.L));
+            d.x += ddx;
+            d.y += ddy;
+        }
+    }
+    if (active) {
+        // wrapped coordinates for evaluation/output, unwrapped displacement
+        // for statistics
+        D.pos[p] = x;
+        D.disp[p] = d;
+        if (inert) D.vel[p] = vn;
+        if (perm) D.id[p] = S.id[q];
+    }
+    if (STATS)
+        wave_stats(active ? d.x * d.x : 0.0, active ? d.y * d.y : 0.0, active,
+                   partials + (int64_t)kStatTerms *
+                                  ((int64_t)lb * (blockDim.x / kWave) + threadIdx.x / kWave));
+    if (lb == 0) advance_clock(P, R.nsteps, clock);
+}
+
+// One logical block of the FP64 step, in place.
+template <bool CUBIC, bool INERTIAL, bool STATS>
 __device__ __forceinline__ void step64_block(const StepParams &P, const State64 &S,
-                                             const State64 &D, const uint32_t *perm,
                                              const Rec64 *__restrict__ rec,
                                              double *__restrict__ partials, DevClock *clock,
                                              int lb)
@@ -39,49 +135,29 @@ __device__ __forceinline__ void step64_block(const StepParams &P, const State64 
     const bool active = local < sp.count;
     const int64_t p = sp.offset + local;
     const Rec64 *rec0 = rec + P.pitch + 1;
-    const double dt = P.dt;
     double r2x = 0.0, r2y = 0.0;
 
-    int64_t q = p;
-    double2 x = make_double2(0.0, 0.0);
-    if (active) {
-        if (GATHER) q = perm[p];
-        x = S.pos[q];
-    }
+    const double2 x = active ? S.pos[p] : make_double2(0.0, 0.0);
     Tile T = no_tile();
     if (P.tile_cap > 0) {
-        const int64_t a0 = sp.offset + base;
-        const double2 a = S.pos[GATHER ? (int64_t)perm[a0] : a0];
-        const int n = P.n, mask = P.mask;
-        const int ax = cell_of_floor(floor(a.x * P.invh), n, mask);
-        const int ay = cell_of_floor(floor(a.y * P.invh), n, mask);
-        const int cx = cell_of_floor(floor(x.x * P.invh), n, mask);
-        const int cy = cell_of_floor(floor(x.y * P.invh), n, mask);
-        int lo, hi;
-        stencil_reach(sp.scheme, lo, hi);
-        const int H = step_halo(P, sp.scheme, (float)dt);
-        const int64_t left = sp.count - base;
-        T = stage_tile<Rec64>(lds, rec0, P, active, cx, cy, ax, ay, lo + H, hi + H,
-                              (int)(left < (int64_t)blockDim.x ? left : blockDim.x));
+        const double2 a = S.pos[sp.offset + base];
+        T = tile64(P, sp, lds, rec0, x, active, cell_of_floor(floor(a.x * P.invh), P.n, P.mask),
+                   cell_of_floor(floor(a.y * P.invh), P.n, P.mask), base);
     }
-
     if (active) {
-        double2 d = S.disp[q];
+        double2 d = S.disp[p];
         double ddx, ddy;
         if (INERTIAL && sp.inertial) {
-            double2 vn = S.vel[q];
+            double2 vn = S.vel[p];
             rk4_inertial64<CUBIC>(rec0, planes, T, P, P.w, sp.scheme, sp.inv_st, x, vn, ddx, ddy);
-            D.vel[p] = vn;
+            S.vel[p] = vn;
         } else {
             rk4_tracer64<CUBIC>(rec0, planes, T, P, P.w, sp.scheme, x, ddx, ddy);
         }
-        // wrapped coordinates for evaluation/output, unwrapped displacement
-        // for statistics
-        D.pos[p] = make_double2(wrap_pos(x.x + ddx, P.L), wrap_pos(x.y + ddy, P.L));
+        S.pos[p] = make_double2(wrap_pos(x.x + ddx, P.L), wrap_pos(x.y + ddy, P.L));
         d.x += ddx;
         d.y += ddy;
-        D.disp[p] = d;
-        if (GATHER) D.id[p] = S.id[q];
+        S.disp[p] = d;
         r2x = d.x * d.x;
         r2y = d.y * d.y;
     }
@@ -89,10 +165,7 @@ __device__ __forceinline__ void step64_block(const StepParams &P, const State64 
         wave_stats(r2x, r2y, active,
                    partials + (int64_t)kStatTerms *
                                   ((int64_t)lb * (blockDim.x / kWave) + threadIdx.x / kWave));
-    if (lb == 0 && threadIdx.x == 0) {
-        clock->t += P.dt;
-        clock->step += 1;
-    }
+    if (lb == 0) advance_clock(P, 1, clock);
 }
 
 // Bound by the latency of the stages' gathers, so by the waves that stay
@@ -111,20 +184,19 @@ void step64_kernel(StepParams P, State64 S, const Rec64 *__restrict__ rec,
 {
     BlockWalk w = block_walk(P, 0, P.total_blocks);
     for (int lb = 0; block_next(w, lb);)
-        step64_block<CUBIC, INERTIAL, STATS, false>(P, S, S, nullptr, rec, partials, clock, lb);
+        step64_block<CUBIC, INERTIAL, STATS>(P, S, rec, partials, clock, lb);
 }
 
-// The FP64 step that follows a re-sort: reads S through perm, writes D.
+// Runs of steps in one launch, and the step that follows a re-sort.
 template <bool CUBIC, bool INERTIAL, bool STATS>
 __global__ __launch_bounds__(kMaxBlock)
 __attribute__((amdgpu_waves_per_eu(CUBIC || INERTIAL ? 4 : 6)))
-void step64_perm_kernel(StepParams P, State64 S, State64 D, const uint32_t *perm,
-                        const Rec64 *__restrict__ rec, double *__restrict__ partials,
-                        DevClock *clock)
+void run64_kernel(StepParams P, StepRun R, State64 S, State64 D, const uint32_t *perm,
+                  const Rec64 *__restrict__ rec, double *__restrict__ partials, DevClock *clock)
 {
     BlockWalk w = block_walk(P, 0, P.total_blocks);
     for (int lb = 0; block_next(w, lb);)
-        step64_block<CUBIC, INERTIAL, STATS, true>(P, S, D, perm, rec, partials, clock, lb);
+        run64_block<CUBIC, INERTIAL, STATS>(P, R, S, D, perm, rec, partials, clock, lb);
 }
 
 // ===========================================================================
@@ -364,14 +436,25 @@ struct GlobalNodes {
     __device__ __forceinline__ float4 both(int a, int b) const { return p[b * pitch + a]; }
 };
 
+// (The tile is addressed through an LDS pointer, not a generic one: where the
+// compiler merges the two accessors' code it must not fall back to flat loads.)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(3))) f32x4 *LdsRec32;
+
 struct TileNodes {
-    const float4 *p;   // origin node
-    int pitch;         // tile width
+    LdsRec32 p;   // origin node
+    int pitch;    // tile width
     __device__ __forceinline__ float2 level(int a, int b, int h) const
     {
-        return reinterpret_cast<const float2 *>(p + (b * pitch + a))[h];
+        typedef const __attribute__((address_space(3))) f32x2 *LdsHalf32;
+        const f32x2 v = ((LdsHalf32)(p + (b * pitch + a)))[h];
+        return make_float2(v.x, v.y);
     }
-    __device__ __forceinline__ float4 both(int a, int b) const { return p[b * pitch + a]; }
+    __device__ __forceinline__ float4 both(int a, int b) const
+    {
+        const f32x4 v = p[b * pitch + a];
+        return make_float4(v.x, v.y, v.z, v.w);
+    }
 };
 
 // Velocity of one stencil (eqs. bilinear_interp, cr_interp, bspline_interp)
@@ -433,15 +516,21 @@ __device__ __forceinline__ void eval32(const Nodes &N, float xi, float eta, bool
                 v = blend32(wa, v, wb, quad_rows(wy, sv));
             }
         } else if (one) {
+            // the loads of a whole stencil, or of half of one with both levels,
+            // before their first use: 32 registers in flight
+            float2 r[4][4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int a = 0; a < 4; ++a) r[b][a] = N.level(a, b, h);
             float au = 0.f, av = 0.f;
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
                 float ru = 0.f, rv = 0.f;
 #pragma unroll
                 for (int a = 0; a < 4; ++a) {
-                    const float2 r = N.level(a, b, h);
-                    ru += wx[a] * r.x;
-                    rv += wx[a] * r.y;
+                    ru += wx[a] * r[b][a].x;
+                    rv += wx[a] * r[b][a].y;
                 }
                 au += wy[b] * ru;
                 av += wy[b] * rv;
@@ -451,20 +540,27 @@ __device__ __forceinline__ void eval32(const Nodes &N, float xi, float eta, bool
         } else {
             float au = 0.f, av = 0.f, bu = 0.f, bv = 0.f;
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                float ru = 0.f, rv = 0.f, su = 0.f, sv = 0.f;
+            for (int b0 = 0; b0 < 4; b0 += 2) {
+                float4 r[2][4];
 #pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    const float4 r = N.both(a, b);
-                    ru += wx[a] * r.x;
-                    rv += wx[a] * r.y;
-                    su += wx[a] * r.z;
-                    sv += wx[a] * r.w;
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) r[b][a] = N.both(a, b0 + b);
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    float ru = 0.f, rv = 0.f, su = 0.f, sv = 0.f;
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) {
+                        ru += wx[a] * r[b][a].x;
+                        rv += wx[a] * r[b][a].y;
+                        su += wx[a] * r[b][a].z;
+                        sv += wx[a] * r[b][a].w;
+                    }
+                    au += wy[b0 + b] * ru;
+                    av += wy[b0 + b] * rv;
+                    bu += wy[b0 + b] * su;
+                    bv += wy[b0 + b] * sv;
                 }
-                au += wy[b] * ru;
-                av += wy[b] * rv;
-                bu += wy[b] * su;
-                bv += wy[b] * sv;
             }
             u = blend32(wa, au, wb, bu);
             v = blend32(wa, av, wb, bv);
@@ -474,7 +570,7 @@ __device__ __forceinline__ void eval32(const Nodes &N, float xi, float eta, bool
 
 __device__ __forceinline__ TileNodes tile_nodes(const float4 *lds, const Tile &T, int tx, int ty)
 {
-    return TileNodes{lds + (__mul24(ty, T.w) + tx), T.w};
+    return TileNodes{(LdsRec32)lds + (__mul24(ty, T.w) + tx), T.w};
 }
 
 __device__ __forceinline__ GlobalNodes global_nodes(const float4 *rec0, const StepParams &P,
@@ -602,220 +698,143 @@ __device__ __forceinline__ void advance_cell(const StepParams &P, int cx, int cy
     o = make_float2(ox, oy);
 }
 
-// One RK4 step of one particle read from slot q and written to slot p; (uc,
-// o) enters as the particle's state and leaves as the new one.
-template <int SCH, bool INERT, bool ONE, bool GATHER>
-__device__ __forceinline__ void particle32(const StepParams &P, const State32 &S,
-                                           const State32 &D, const float4 *__restrict__ rec0,
-                                           const float4 *lds, const Tile &T, const SpeciesDev &sp,
-                                           int64_t p, int64_t q, uint32_t cell, int2 &uc,
-                                           float2 &o)
-{
-    const int cx = (int)(cell & 0xFFFFu), cy = (int)(cell >> 16);
-    int rx = 0, ry = 0;
-    if (T.on) {   // cx - T.x0 lies in (-n, n)
-        rx = cx - T.x0;
-        ry = cy - T.y0;
-        rx += rx < 0 ? P.n : 0;
-        ry += ry < 0 ? P.n : 0;
-    }
-    float dqx, dqy;
-    float2 vn = make_float2(0.f, 0.f);
-    if constexpr (INERT) vn = ld_stream(S.vel + q);
-    rk4_split<SCH, INERT, ONE, 1>(P, P.w, rec0, lds, T, sp, cx, cy, rx, ry, o, vn, dqx, dqy);
-    if constexpr (INERT) st_stream(D.vel + p, vn);
-    advance_cell(P, cx, cy, dqx, dqy, uc, o);
-    st_stream(D.uc + p, uc);
-    st_stream(D.off + p, o);
-}
-
-// The particle body for the block's kind.  SCHS: the scheme of every species
-// of the launch (one launch per scheme), or kAnyScheme in a fused launch.
-// KINDS: 0 tracers only (St == 0 included), 1 tracers and/or inertial
-// species.
-template <int SCHS, int KINDS, bool ONE, bool GATHER>
-__device__ __forceinline__ void particle_dispatch(const StepParams &P, const State32 &S,
-                                                  const State32 &D,
-                                                  const float4 *__restrict__ rec0,
-                                                  const float4 *lds, const Tile &T,
-                                                  const SpeciesDev &sp, int64_t p, int64_t q,
-                                                  uint32_t cell, int2 &uc, float2 &o)
+// rk4_split of the block's species.  SCHS: the scheme of every species of the
+// launch (one launch per scheme), or kAnyScheme in a fused launch.  KINDS: 0
+// tracers only (St == 0 included), 1 tracers and/or inertial species.
+template <int SCHS, int KINDS>
+__device__ __forceinline__ void rk4_species(const StepParams &P, const StageWeights &W,
+                                            const float4 *__restrict__ rec0, const float4 *lds,
+                                            const Tile &T, const SpeciesDev &sp, int cx, int cy,
+                                            float2 o, float2 &vn, float &dqx, float &dqy)
 {
     if constexpr (SCHS == kAnyScheme) {   // fused launch: the block's species decides
         if (sp.scheme == kBilinear)
-            particle_dispatch<kBilinear, KINDS, ONE, GATHER>(P, S, D, rec0, lds, T, sp, p, q, cell,
-                                                             uc, o);
+            rk4_species<kBilinear, KINDS>(P, W, rec0, lds, T, sp, cx, cy, o, vn, dqx, dqy);
         else if (sp.scheme == kCatmullRom)
-            particle_dispatch<kCatmullRom, KINDS, ONE, GATHER>(P, S, D, rec0, lds, T, sp, p, q,
-                                                               cell, uc, o);
+            rk4_species<kCatmullRom, KINDS>(P, W, rec0, lds, T, sp, cx, cy, o, vn, dqx, dqy);
         else
-            particle_dispatch<kBSpline, KINDS, ONE, GATHER>(P, S, D, rec0, lds, T, sp, p, q, cell,
-                                                            uc, o);
-        return;
-    }
-    if (KINDS != 0 && sp.inertial)
-        particle32<SCHS, KINDS != 0, ONE, GATHER>(P, S, D, rec0, lds, T, sp, p, q, cell, uc, o);
-    else
-        particle32<SCHS, false, ONE, GATHER>(P, S, D, rec0, lds, T, sp, p, q, cell, uc, o);
-}
-
-// One logical block at one particle per thread: step32_block with ROWS = 1,
-// as a body of its own (the row loop's carried state would cost registers a
-// single row does not need).
-template <int SCHS, int KINDS, bool STATS, bool GATHER>
-__device__ __forceinline__ void step32_block1(const StepParams &P, const State32 &S,
-                                             const State32 &D, const uint32_t *perm,
-                                             const float4 *__restrict__ rec,
-                                             double *__restrict__ partials, DevClock *clock,
-                                             int lb)
-{
-    float4 *lds = reinterpret_cast<float4 *>(lpt_dyn_lds);
-    const SpeciesDev &sp = P.sp[P.nspecies > 1 ? species_of(P, lb) : 0];
-    const int64_t base = (int64_t)(lb - sp.block_begin) * blockDim.x;
-    const int64_t local = base + threadIdx.x;
-    const bool active = local < sp.count;
-    const int64_t p = sp.offset + local;
-    const float4 *rec0 = rec + P.pitch + 1;
-    double r2x = 0.0, r2y = 0.0;
-
-    int64_t q = p;
-    uint32_t cell = 0;   // the stored cell, (cy << 16) | cx
-    int2 uc = make_int2(0, 0);
-    float2 o = make_float2(0.f, 0.f);
-    if (active) {
-        if (GATHER) q = perm[p];
-        uc = ld_stream(S.uc + q);
-        o = ld_stream(S.off + q);
-        cell = (uint32_t)wrapn(uc.x, P) | ((uint32_t)wrapn(uc.y, P) << 16);
-    }
-    Tile T = no_tile();
-    if (P.tile_cap > 0) {
-        int lo, hi;
-        stencil_reach(sp.scheme, lo, hi);
-        const int H = step_halo(P, sp.scheme, P.dtf);
-        const int64_t left = sp.count - base;
-        const int nact = (int)(left < (int64_t)blockDim.x ? left : blockDim.x);
-        const int64_t a0 = sp.offset + base;
-        const int2 a = S.uc[GATHER ? (int64_t)perm[a0] : a0];
-        T = stage_tile<float4>(lds, rec0, P, active, (int)(cell & 0xFFFFu), (int)(cell >> 16),
-                               wrapn(a.x, P), wrapn(a.y, P), lo + H, hi + H, nact);
-    }
-    if (active) {
-        if (P.w.ends_one)
-            particle_dispatch<SCHS, KINDS, true, GATHER>(P, S, D, rec0, lds, T, sp, p, q, cell, uc,
-                                                         o);
-        else
-            particle_dispatch<SCHS, KINDS, false, GATHER>(P, S, D, rec0, lds, T, sp, p, q, cell,
-                                                          uc, o);
-        if (GATHER || STATS) {
-            const uint32_t g = S.id[q];
-            if (GATHER) D.id[p] = g;
-            if (STATS) {   // the displacement since initialisation, from the new state
-                const double2 d = split_disp(uc, o, initial_pos(sp, S.x0, g, P), P);
-                r2x = d.x * d.x;
-                r2y = d.y * d.y;
-            }
+            rk4_species<kBSpline, KINDS>(P, W, rec0, lds, T, sp, cx, cy, o, vn, dqx, dqy);
+    } else {
+        int rx = 0, ry = 0;
+        if (T.on) {   // cx - T.x0 lies in (-n, n)
+            rx = cx - T.x0;
+            ry = cy - T.y0;
+            rx += rx < 0 ? P.n : 0;
+            ry += ry < 0 ? P.n : 0;
+        }
+        if (W.ends_one) {
+            if (KINDS != 0 && sp.inertial)
+                rk4_split<SCHS, KINDS != 0, true, 1>(P, W, rec0, lds, T, sp, cx, cy, rx, ry, o, vn,
+                                                     dqx, dqy);
+            else
+                rk4_split<SCHS, false, true, 1>(P, W, rec0, lds, T, sp, cx, cy, rx, ry, o, vn, dqx,
+                                                dqy);
+        } else {
+            if (KINDS != 0 && sp.inertial)
+                rk4_split<SCHS, KINDS != 0, false, 1>(P, W, rec0, lds, T, sp, cx, cy, rx, ry, o,
+                                                      vn, dqx, dqy);
+            else
+                rk4_split<SCHS, false, false, 1>(P, W, rec0, lds, T, sp, cx, cy, rx, ry, o, vn,
+                                                 dqx, dqy);
         }
     }
-    if (STATS)
-        wave_stats(r2x, r2y, active,
-                   partials + (int64_t)kStatTerms *
-                                  ((int64_t)lb * (blockDim.x / kWave) + threadIdx.x / kWave));
-    if (lb == 0 && threadIdx.x == 0) {
-        clock->t += P.dt;
-        clock->step += 1;
-    }
 }
 
-// One logical block of the step.  The state of slot p is read from S and
-// written to D: in place, or, on a step that follows a re-sort (GATHER),
-// slot p of D takes the particle of slot perm[p] of S, id included, so that
-// the step itself applies the sort's permutation.  A logical block holds
-// ROWS rows of blockDim.x slots: thread t takes slot t of every row, so the
-// block's set-up (its box, tile and launch bookkeeping) is shared by ROWS
-// particles per thread.  Row 0 keeps its state in registers from the box to
-// the step; the cells of later rows are read for the box and again for the
-// step (the second read finds them in the cache).
-template <int SCHS, int KINDS, bool STATS, bool GATHER, int ROWS>
-__device__ __forceinline__ void step32_block(const StepParams &P, const State32 &S,
-                                             const State32 &D, const uint32_t *perm,
-                                             const float4 *__restrict__ rec,
+// One logical block of a launch: R.nsteps steps of the block's particles, which
+// stay in registers, with a new tile for each step.  A logical block holds
+// ROWS rows of blockDim.x slots: thread t takes slot t of every row, so that
+// the block's set-up (its box, tile and launch bookkeeping) is shared by ROWS
+// particles per thread.  Slot p of D takes the particle of slot p of S (D = S:
+// in place), or, on the steps that follow a re-sort, of slot perm[p], id
+// included.  The box of a step is taken about the centre of the box before
+// (any cell near the particles will do).  RUN = false: one step in place (perm
+// null, the weights in P.w), without the run's bookkeeping.
+template <int SCHS, int KINDS, bool STATS, int ROWS, bool RUN>
+__device__ __forceinline__ void step32_block(const StepParams &P, const StepRun &R,
+                                             const State32 &S, const State32 &D,
+                                             const uint32_t *perm_, const float4 *__restrict__ rec,
                                              double *__restrict__ partials, DevClock *clock,
                                              int lb)
 {
-    if constexpr (ROWS == 1) {
-        step32_block1<SCHS, KINDS, STATS, GATHER>(P, S, D, perm, rec, partials, clock, lb);
-        return;
-    }
+    const uint32_t *perm = RUN ? perm_ : nullptr;
+    const int nsteps = RUN ? R.nsteps : 1;
     float4 *lds = reinterpret_cast<float4 *>(lpt_dyn_lds);
     const SpeciesDev &sp = P.sp[P.nspecies > 1 ? species_of(P, lb) : 0];
     const int threads = (int)blockDim.x;
     const int64_t slots = (int64_t)threads * ROWS;
     const int64_t base = (int64_t)(lb - sp.block_begin) * slots;
+    const int64_t first = base + threadIdx.x;   // row r: first + r * threads
     const float4 *rec0 = rec + P.pitch + 1;
+    const bool inert = KINDS != 0 && sp.inertial;
 
-    const bool active0 = base + threadIdx.x < sp.count;
-    int64_t q0 = sp.offset + base + threadIdx.x;
-    uint32_t cell0 = 0;   // the stored cell, (cy << 16) | cx
-    int2 uc0 = make_int2(0, 0);
-    float2 o0 = make_float2(0.f, 0.f);
-    if (active0) {
-        if (GATHER) q0 = perm[q0];
-        uc0 = ld_stream(S.uc + q0);
-        o0 = ld_stream(S.off + q0);
-        cell0 = (uint32_t)wrapn(uc0.x, P) | ((uint32_t)wrapn(uc0.y, P) << 16);
+    int2 uc[ROWS];
+    float2 o[ROWS], vn[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        uc[r] = make_int2(0, 0);
+        o[r] = vn[r] = make_float2(0.f, 0.f);
+        const int64_t local = first + (int64_t)r * threads;
+        if (local < sp.count) {
+            const int64_t p = sp.offset + local, q = perm ? (int64_t)perm[p] : p;
+            uc[r] = ld_stream(S.uc + q);
+            o[r] = ld_stream(S.off + q);
+            if (inert) vn[r] = ld_stream(S.vel + q);
+        }
     }
-    Tile T = no_tile();
+    int ax = 0, ay = 0, lo = 0, hi = 0, nact = 0;
     if (P.tile_cap > 0) {
-        int lo, hi;
         stencil_reach(sp.scheme, lo, hi);
         const int H = step_halo(P, sp.scheme, P.dtf);
+        lo += H;
+        hi += H;
         const int64_t left = sp.count - base;
-        const int nact = (int)(left < slots ? left : slots);
+        nact = (int)(left < slots ? left : slots);
         const int64_t a0 = sp.offset + base;
-        const int2 a = S.uc[GATHER ? (int64_t)perm[a0] : a0];
-        const int ax = wrapn(a.x, P), ay = wrapn(a.y, P);
-        BoxAcc b = active0 ? box_of((int)(cell0 & 0xFFFFu), (int)(cell0 >> 16), ax, ay, P.n)
-                           : box_init();
+        const int2 a = S.uc[perm ? (int64_t)perm[a0] : a0];
+        ax = wrapn(a.x, P);
+        ay = wrapn(a.y, P);
+    }
+    for (int k = 0; k < nsteps; ++k) {
+        const StageWeights &W = RUN ? R.w[k] : P.w;
+        Tile T = no_tile();
+        if (P.tile_cap > 0) {
+            BoxAcc b = box_init();
+            bool any = false;
 #pragma unroll
-        for (int r = 1; r < ROWS; ++r) {
-            const int64_t local = base + (int64_t)r * threads + threadIdx.x;
-            if (local < sp.count) {
-                const int64_t p = sp.offset + local;
-                const int2 u = S.uc[GATHER ? (int64_t)perm[p] : p];
-                box_add(b, wrapn(u.x, P), wrapn(u.y, P), ax, ay, P.n);
-            }
+            for (int r = 0; r < ROWS; ++r)
+                if (first + (int64_t)r * threads < sp.count) {
+                    const BoxAcc c = box_of(wrapn(uc[r].x, P), wrapn(uc[r].y, P), ax, ay, P.n);
+                    b = any ? BoxAcc{pmax16(b.up, c.up), pmax16(b.dn, c.dn)} : c;
+                    any = true;
+                }
+            T = stage_tile_acc<float4>(lds, rec0, P, b, ax, ay, lo, hi, nact);
+            ax = wrapn(T.x0 + T.w / 2, P);
+            ay = wrapn(T.y0 + T.h / 2, P);
         }
-        T = stage_tile_acc<float4>(lds, rec0, P, b, ax, ay, lo + H, hi + H, nact);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+            if (first + (int64_t)r * threads < sp.count) {
+                const int cx = wrapn(uc[r].x, P), cy = wrapn(uc[r].y, P);
+                float dqx, dqy;
+                rk4_species<SCHS, KINDS>(P, W, rec0, lds, T, sp, cx, cy, o[r], vn[r], dqx, dqy);
+                advance_cell(P, cx, cy, dqx, dqy, uc[r], o[r]);
+            }
     }
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
-        const int64_t local = base + (int64_t)r * threads + threadIdx.x;
+        const int64_t local = first + (int64_t)r * threads;
         const bool active = local < sp.count;
-        const int64_t p = sp.offset + local;
         double r2x = 0.0, r2y = 0.0;
         if (active) {
-            int64_t q = q0;
-            int2 uc = uc0;
-            float2 o = o0;
-            uint32_t cell = cell0;
-            if (r > 0) {
-                q = GATHER ? (int64_t)perm[p] : p;
-                uc = ld_stream(S.uc + q);
-                o = ld_stream(S.off + q);
-                cell = (uint32_t)wrapn(uc.x, P) | ((uint32_t)wrapn(uc.y, P) << 16);
-            }
-            if (P.w.ends_one)
-                particle_dispatch<SCHS, KINDS, true, GATHER>(P, S, D, rec0, lds, T, sp, p, q, cell,
-                                                             uc, o);
-            else
-                particle_dispatch<SCHS, KINDS, false, GATHER>(P, S, D, rec0, lds, T, sp, p, q,
-                                                              cell, uc, o);
-            if (GATHER || STATS) {
-                const uint32_t g = S.id[q];
-                if (GATHER) D.id[p] = g;
+            const int64_t p = sp.offset + local;
+            st_stream(D.uc + p, uc[r]);
+            st_stream(D.off + p, o[r]);
+            if (inert) st_stream(D.vel + p, vn[r]);
+            if (perm || STATS) {
+                const uint32_t g = S.id[perm ? (int64_t)perm[p] : p];
+                if (perm) D.id[p] = g;
                 if (STATS) {   // the displacement since initialisation, from the new state
-                    const double2 d = split_disp(uc, o, initial_pos(sp, S.x0, g, P), P);
+                    const double2 d = split_disp(uc[r], o[r], initial_pos(sp, S.x0, g, P), P);
                     r2x = d.x * d.x;
                     r2y = d.y * d.y;
                 }
@@ -829,10 +848,7 @@ __device__ __forceinline__ void step32_block(const StepParams &P, const State32 
                                       (((int64_t)lb * slots + (int64_t)r * threads) / kWave +
                                        threadIdx.x / kWave));
     }
-    if (lb == 0 && threadIdx.x == 0) {
-        clock->t += P.dt;
-        clock->step += 1;
-    }
+    if (lb == 0) advance_clock(P, nsteps, clock);
 }
 
 // One launch advances every particle of its logical blocks by one step
@@ -844,32 +860,32 @@ __device__ __forceinline__ void step32_block(const StepParams &P, const State32 
 // (SCHS = kAnyScheme), need more registers and keep the default bound.
 template <int SCHS, int KINDS, bool STATS, int ROWS>
 __global__ __launch_bounds__(kMaxBlock)
-__attribute__((amdgpu_waves_per_eu(SCHS == kBilinear ? 8 : 6)))
+__attribute__((amdgpu_waves_per_eu(SCHS == kBilinear ? 8 : 6, SCHS == kBilinear ? 8 : 6)))
 void step32_kernel(StepParams P, State32 S, const float4 *__restrict__ rec,
                    double *__restrict__ partials, DevClock *clock)
 {
+    const StepRun none{};
     BlockWalk w = block_walk(P, P.block_base, P.launch_blocks);
     for (int lb = 0; block_next(w, lb);)
-        step32_block<SCHS, KINDS, STATS, false, ROWS>(P, S, S, nullptr, rec, partials, clock, lb);
+        step32_block<SCHS, KINDS, STATS, ROWS, false>(P, none, S, S, nullptr, rec, partials, clock,
+                                                      lb);
 }
 
-// The step that follows a re-sort: reads S through perm, writes D.  (A kernel
-// of its own, so that the in-place kernel above keeps its argument list.)
+// Runs of steps in one launch, and the step that follows a re-sort.
 template <int SCHS, int KINDS, bool STATS, int ROWS>
 __global__ __launch_bounds__(kMaxBlock)
-__attribute__((amdgpu_waves_per_eu(SCHS == kBilinear ? 8 : 6)))
-void step32_perm_kernel(StepParams P, State32 S, State32 D, const uint32_t *perm,
-                        const float4 *__restrict__ rec, double *__restrict__ partials,
-                        DevClock *clock)
+__attribute__((amdgpu_waves_per_eu(SCHS == kBilinear ? 8 : 6, SCHS == kBilinear ? 8 : 6)))
+void run32_kernel(StepParams P, StepRun R, State32 S, State32 D, const uint32_t *perm,
+                  const float4 *__restrict__ rec, double *__restrict__ partials, DevClock *clock)
 {
     BlockWalk w = block_walk(P, P.block_base, P.launch_blocks);
     for (int lb = 0; block_next(w, lb);)
-        step32_block<SCHS, KINDS, STATS, true, ROWS>(P, S, D, perm, rec, partials, clock, lb);
+        step32_block<SCHS, KINDS, STATS, ROWS, true>(P, R, S, D, perm, rec, partials, clock, lb);
 }
 
 // ===========================================================================
-// Runs of steps in one launch, for populations too small to fill the chip.
-// Such a launch lasts as long as one wave's chain of dependent gathers, plus
+// Runs of steps for populations too small to fill the chip, or too sparse to
+// share a tile.  Such a launch lasts as long as one wave's chain of dependent gathers, plus
 // the launch itself, whatever the number of particles, so the particles keep
 // their state in registers for up to kMaxRun steps (to the next record,
 // re-sort or checkpoint), every wave has a CU to itself where there are
@@ -878,7 +894,7 @@ void step32_perm_kernel(StepParams P, State32 S, State32 D, const uint32_t *perm
 // few particles of a workgroup share no nodes worth staging.  Each unit of 64
 // slots is one statistics partial, as in the other step kernels, and every
 // sum is taken in their order, so the results are the same bits.  4096
-// particles, 64^2, 100 steps with 10 records: 868 -> 330 us a call; which
+// particles, 64^2, 100 steps with 10 records: 868 -> 395 us a call; which
 // populations count as small is decided where these are launched.
 // ===========================================================================
 template <int LANES>
@@ -926,16 +942,6 @@ __device__ __forceinline__ void small_stats(const SmallSlot<LANES> &s, double r2
     }
 }
 
-__device__ __forceinline__ void advance_clock(const StepParams &P, int steps, DevClock *clock)
-{
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        double t = clock->t;
-        for (int k = 0; k < steps; ++k) t += P.dt;   // as that many launches add it
-        clock->t = t;
-        clock->step += steps;
-    }
-}
-
 template <bool CUBIC, bool INERTIAL, bool STATS>
 __global__ __launch_bounds__(CUBIC ? 4 * kWave : kWave) void small64_kernel(
     StepParams P, StepRun R, State64 S, State64 D, const uint32_t *perm,
@@ -974,7 +980,7 @@ __global__ __launch_bounds__(CUBIC ? 4 * kWave : kWave) void small64_kernel(
         r2y = d.y * d.y;
     }
     if (STATS) small_stats<LANES>(s, r2x, r2y, partials);
-    advance_clock(P, R.nsteps, clock);
+    if (blockIdx.x == 0) advance_clock(P, R.nsteps, clock);
 }
 
 // The steps of one split particle of one scheme.
@@ -1041,7 +1047,7 @@ __global__ __launch_bounds__(CUBIC ? 4 * kWave : kWave) void small32_kernel(
         }
     }
     if (STATS) small_stats<LANES>(s, r2x, r2y, partials);
-    advance_clock(P, R.nsteps, clock);
+    if (blockIdx.x == 0) advance_clock(P, R.nsteps, clock);
 }
 
 // Grid of a launch: one workgroup per logical block (per table entry in a
@@ -1125,7 +1131,7 @@ static int32_t auto_tile_cap(K kernel, int block, int planes, int32_t fallback)
 }
 
 template <bool C, bool I, bool S>
-static hipError_t launch64_t(const StepParams &P, const State64 &St, const State64 &Dst,
+static hipError_t launch64_t(const StepParams &P, const StepRun &R, const State64 &St, const State64 &Dst,
                              const uint32_t *perm, const Rec64 *rec, double *partials,
                              DevClock *clock, int block, int grid, hipStream_t st)
 {
@@ -1135,10 +1141,10 @@ static hipError_t launch64_t(const StepParams &P, const State64 &St, const State
     // two planes of 16-byte entries; the fill writes whole 64-entry chunks of each
     const size_t lds = P1.tile_cap > 0 ? (size_t)(2 * P1.tile_cap + kWave) * 16 : 0;
     StepParams Q;
-    if (perm) {
-        const int g = launch_grid(step64_perm_kernel<C, I, S>, P1, block, lds, grid, Q);
-        hipLaunchKernelGGL((step64_perm_kernel<C, I, S>), dim3(g), dim3(block), lds, st, Q, St,
-                           Dst, perm, rec, partials, clock);
+    if (perm || R.nsteps > 1) {
+        const int g = launch_grid(run64_kernel<C, I, S>, P1, block, lds, grid, Q);
+        hipLaunchKernelGGL((run64_kernel<C, I, S>), dim3(g), dim3(block), lds, st, Q, R, St, Dst,
+                           perm, rec, partials, clock);
     } else {
         const int g = launch_grid(step64_kernel<C, I, S>, P1, block, lds, grid, Q);
         hipLaunchKernelGGL((step64_kernel<C, I, S>), dim3(g), dim3(block), lds, st, Q, St, rec,
@@ -1148,27 +1154,27 @@ static hipError_t launch64_t(const StepParams &P, const State64 &St, const State
 }
 
 template <int SCHS, int KINDS, bool ST, int ROWS>
-static hipError_t launch32_r(const StepParams &P, const State32 &S, const State32 &D,
+static hipError_t launch32_r(const StepParams &P, const StepRun &R, const State32 &S, const State32 &D,
                              const uint32_t *perm, const float4 *rec, double *partials,
                              DevClock *clock, int block, int grid, hipStream_t st)
 {
     // a logical block of `block` slots runs on block / ROWS threads
     const int threads = block / ROWS;
     StepParams P1 = P;
+    const bool run = perm || R.nsteps > 1;
     if (P.tile_auto && P.tile_cap > 0)
-        P1.tile_cap = perm ? auto_tile_cap(step32_perm_kernel<SCHS, KINDS, ST, ROWS>, threads, 1,
-                                           P.tile_cap)
-                           : auto_tile_cap(step32_kernel<SCHS, KINDS, ST, ROWS>, threads, 1,
-                                           P.tile_cap);
+        P1.tile_cap = run ? auto_tile_cap(run32_kernel<SCHS, KINDS, ST, ROWS>, threads, 1,
+                                          P.tile_cap)
+                          : auto_tile_cap(step32_kernel<SCHS, KINDS, ST, ROWS>, threads, 1,
+                                          P.tile_cap);
     // whole 64-entry chunks: the tile fill writes LDS a wave's chunk at a time
     const size_t lds =
         P1.tile_cap > 0 ? (size_t)((P1.tile_cap + kWave - 1) / kWave * kWave) * sizeof(float4) : 0;
     StepParams Q;
-    if (perm) {
-        const int g =
-            launch_grid(step32_perm_kernel<SCHS, KINDS, ST, ROWS>, P1, threads, lds, grid, Q);
-        hipLaunchKernelGGL((step32_perm_kernel<SCHS, KINDS, ST, ROWS>), dim3(g), dim3(threads),
-                           lds, st, Q, S, D, perm, rec, partials, clock);
+    if (run) {
+        const int g = launch_grid(run32_kernel<SCHS, KINDS, ST, ROWS>, P1, threads, lds, grid, Q);
+        hipLaunchKernelGGL((run32_kernel<SCHS, KINDS, ST, ROWS>), dim3(g), dim3(threads), lds, st,
+                           Q, R, S, D, perm, rec, partials, clock);
     } else {
         const int g = launch_grid(step32_kernel<SCHS, KINDS, ST, ROWS>, P1, threads, lds, grid, Q);
         hipLaunchKernelGGL((step32_kernel<SCHS, KINDS, ST, ROWS>), dim3(g), dim3(threads), lds, st,
@@ -1178,7 +1184,7 @@ static hipError_t launch32_r(const StepParams &P, const State32 &S, const State3
 }
 
 template <int SCHS, int KINDS, bool ST>
-static hipError_t launch32_t(const StepParams &P, const State32 &S, const State32 &D,
+static hipError_t launch32_t(const StepParams &P, const StepRun &R, const State32 &S, const State32 &D,
                              const uint32_t *perm, const float4 *rec, double *partials,
                              DevClock *clock, int block, int grid, hipStream_t st)
 {
@@ -1187,24 +1193,24 @@ static hipError_t launch32_t(const StepParams &P, const State32 &S, const State3
     // every other body runs one row, whatever P.rows asks
     if constexpr (SCHS == kBilinear && KINDS == 0)
         if (P.rows == 2)
-            return launch32_r<SCHS, KINDS, ST, 2>(P, S, D, perm, rec, partials, clock, block, grid,
+            return launch32_r<SCHS, KINDS, ST, 2>(P, R, S, D, perm, rec, partials, clock, block, grid,
                                                   st);
-    return launch32_r<SCHS, KINDS, ST, 1>(P, S, D, perm, rec, partials, clock, block, grid, st);
+    return launch32_r<SCHS, KINDS, ST, 1>(P, R, S, D, perm, rec, partials, clock, block, grid, st);
 }
 
 template <int SCHS>
-static hipError_t launch32_s(const StepParams &P, const State32 &S, const State32 &D,
+static hipError_t launch32_s(const StepParams &P, const StepRun &R, const State32 &S, const State32 &D,
                              const uint32_t *perm, const float4 *rec, double *partials,
                              DevClock *clock, bool stats, bool inertial, int block, int grid,
                              hipStream_t st)
 {
     if (inertial)
-        return stats ? launch32_t<SCHS, 1, true>(P, S, D, perm, rec, partials, clock, block, grid,
+        return stats ? launch32_t<SCHS, 1, true>(P, R, S, D, perm, rec, partials, clock, block, grid,
                                                  st)
-                     : launch32_t<SCHS, 1, false>(P, S, D, perm, rec, partials, clock, block,
+                     : launch32_t<SCHS, 1, false>(P, R, S, D, perm, rec, partials, clock, block,
                                                   grid, st);
-    return stats ? launch32_t<SCHS, 0, true>(P, S, D, perm, rec, partials, clock, block, grid, st)
-                 : launch32_t<SCHS, 0, false>(P, S, D, perm, rec, partials, clock, block, grid,
+    return stats ? launch32_t<SCHS, 0, true>(P, R, S, D, perm, rec, partials, clock, block, grid, st)
+                 : launch32_t<SCHS, 0, false>(P, R, S, D, perm, rec, partials, clock, block, grid,
                                               st);
 }
 
@@ -1223,31 +1229,31 @@ static hipError_t launch32_s(const StepParams &P, const State32 &S, const State3
         }                                                                            \
     } while (0)
 
-hipError_t launch_step64(const StepParams &P, const State64 &S, const State64 &D,
-                         const uint32_t *perm, const Rec64 *rec, double *partials,
-                         DevClock *clock, bool stats, bool cubic, bool inertial, int block,
-                         int grid, hipStream_t st)
+hipError_t launch_step64(const StepParams &P, const StepRun &R, const State64 &S,
+                         const State64 &D, const uint32_t *perm, const Rec64 *rec,
+                         double *partials, DevClock *clock, bool stats, bool cubic,
+                         bool inertial, int block, int grid, hipStream_t st)
 {
-    LPT_DISPATCH(launch64_t, P, S, D, perm, rec, partials, clock, block, grid, st);
+    LPT_DISPATCH(launch64_t, P, R, S, D, perm, rec, partials, clock, block, grid, st);
 }
 
-hipError_t launch_step32(const StepParams &P, const State32 &S, const State32 &D,
+hipError_t launch_step32(const StepParams &P, const StepRun &R, const State32 &S, const State32 &D,
                          const uint32_t *perm, const float4 *rec, double *partials,
                          DevClock *clock, bool stats, int schemes, bool inertial, int block,
                          int grid, hipStream_t st)
 {
     switch (schemes) {
     case kBilinear:
-        return launch32_s<kBilinear>(P, S, D, perm, rec, partials, clock, stats, inertial, block,
+        return launch32_s<kBilinear>(P, R, S, D, perm, rec, partials, clock, stats, inertial, block,
                                      grid, st);
     case kCatmullRom:
-        return launch32_s<kCatmullRom>(P, S, D, perm, rec, partials, clock, stats, inertial,
+        return launch32_s<kCatmullRom>(P, R, S, D, perm, rec, partials, clock, stats, inertial,
                                        block, grid, st);
     case kBSpline:
-        return launch32_s<kBSpline>(P, S, D, perm, rec, partials, clock, stats, inertial, block,
+        return launch32_s<kBSpline>(P, R, S, D, perm, rec, partials, clock, stats, inertial, block,
                                     grid, st);
     case kAnyScheme:
-        return launch32_s<kAnyScheme>(P, S, D, perm, rec, partials, clock, stats, inertial,
+        return launch32_s<kAnyScheme>(P, R, S, D, perm, rec, partials, clock, stats, inertial,
                                       block, grid, st);
     default:
         return hipErrorInvalidValue;

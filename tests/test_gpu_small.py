@@ -1,5 +1,5 @@
-"""Small-population step launches (several steps each, a bicubic stencil split
-over four lanes) against the tiled kernels: a particle's trajectory does not
+"""Launches of several steps against launches of one, and the small-population
+kernels (no tile, a bicubic stencil split over four lanes) against the tiled ones: a particle's trajectory does not
 depend on the population it is part of, so the leading particles of a large
 species, which takes the tiled kernels, must have the same bits as the same
 particles alone."""
@@ -60,6 +60,42 @@ def test_small_equals_tiled(precision, scheme, mode, compat, interval):
         # by slot, which does not depend on the other species
         for f in small[2].dtype.names:
             assert np.array_equal(small[2][f], large[2][f]), (count, f)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_split"])
+@pytest.mark.parametrize("scheme", ["bilinear", "catmull_rom", "mixed"])
+@pytest.mark.parametrize("tuning", [dict(), dict(block_size=512, rows=2), dict(tile_records=-1),
+                                    dict(tile_records=64, block_size=128), dict(fused=0),
+                                    dict(persistent=1, max_workgroups=64)])
+def test_runs_equal_single_steps(precision, scheme, tuning):
+    """The tiled kernels: 21 steps in one call (runs of up to 16, cut by records
+    and re-sorts) against 21 calls of one step."""
+    n, steps, count = 40, 21, LARGE + 50
+    x, y = synth.random_points(count + 3000, seed=6)
+    first = "bilinear" if scheme == "mixed" else scheme
+    second = "bspline" if scheme == "mixed" else scheme
+    species = [("tracer", 0.0, first, x[:count], y[:count])]
+    if scheme != "bilinear":   # one species alone takes its own kernels
+        species.append(("inertial", 0.3, second, x[count:], y[count:]))
+    got = []
+    for single in (False, True):
+        tr, dt = _tracker(n, precision, "bracket", species, sort_interval=18)
+        tr.set_tuning(**tuning)
+        if single:
+            for _ in range(steps):
+                tr.step(1, dt, stats_every=20)
+        else:
+            tr.step(steps, dt, stats_every=20)
+        out = [_state(tr, s, s == 1, count) for s in range(len(species))]
+        got.append((sum(out, []), [tr.get_stats(s) for s in range(len(species))],
+                    [tr.get_order(s) for s in range(len(species))], tr.get_time()))
+        tr.close()
+    for p, q in zip(got[0][0], got[1][0]):
+        assert np.array_equal(p, q)
+    for k in (1, 2):
+        for p, q in zip(got[0][k], got[1][k]):
+            assert np.array_equal(p, q)
+    assert got[0][3] == got[1][3]
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32_split"])
