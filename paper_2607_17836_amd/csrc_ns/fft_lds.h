@@ -1,5 +1,5 @@
-// Complex FFT of N = 64, 128, ..., 4096 FP64 points held in LDS, computed by
-// one workgroup of N / 8 threads.
+// Complex FFT of N = 64, 128, ..., 4096 FP64 points by one workgroup of N / 8
+// threads, eight points a thread, exchanged through LDS between passes.
 //
 // Stockham autosort formulation (Govindaraju et al., "High performance
 // discrete Fourier transforms on graphics processors", SC 2008): pass p of
@@ -9,10 +9,16 @@
 // starting from (j - k) R + k; after the last pass the result is in natural
 // order.  Radix-8 passes and a last 2 or 4 where log2 N is not a multiple of
 // 3 (64 = 8 8, 128 = 8 8 2, 256 = 8 8 4, 512 = 8 8 8, 1024 = 8 8 8 2,
-// 2048 = 8 8 8 4, 4096 = 8 8 8 8).  Each pass first reads all of a
-// thread's inputs into registers, then (after a barrier) writes, so one LDS
-// buffer suffices.  Forward: exp(-2 pi i jk / N); inverse: exp(+2 pi i jk / N),
-// unnormalised.  Twiddles come from a table W[m] = exp(-2 pi i m / N).
+// 2048 = 8 8 8 4, 4096 = 8 8 8 8).  Forward: exp(-2 pi i jk / N); inverse:
+// exp(+2 pi i jk / N), unnormalised.
+//
+// With T = N / 8 threads, thread t's inputs of every pass are the points t + q
+// T, q = 0 .. 7, and so are its outputs of the last one: a transform starts and
+// ends in registers, and only the exchanges between passes touch LDS (three at
+// N = 512 and above; with the points staged in LDS before and after it was
+// five).  Entry i sits at i + i / 8 there, so that the first exchange's stride
+// of eight 16-byte entries spreads over the banks.  Twiddles come from a table
+// per pass, laid out [r - 1][k], so that a wave's reads are contiguous.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -88,59 +94,129 @@ __device__ __forceinline__ void dft(double2 *v)
     else dft2<INV>(v);
 }
 
-// One Stockham pass of radix R with Ns = product of the earlier radices.
-// Entered and left with the block synchronised.
-template <int N, int R, bool INV>
-__device__ __forceinline__ void pass(double2 *buf, int Ns, const double2 *__restrict__ W)
+// LDS entries of one transform's exchange buffer, and the place of entry i.
+template <int N>
+constexpr int lds_entries() { return N + N / 8; }
+__device__ __forceinline__ int pad(int i) { return i + (i >> 3); }
+// Distance of the places of entries i and i + n, for n a multiple of 8.
+constexpr int padded(int n) { return n + n / 8; }
+
+// Radix of the pass that follows NS points (8 unless fewer are left).
+template <int N, int NS>
+constexpr int radix() { return N / NS >= 8 ? 8 : N / NS; }
+
+// Twiddle table of N: for NS = 8, 64, 512 (below N) the (R - 1) NS values
+// exp(-2 pi i r k / (NS R)), r = 1 .. R - 1, k < NS, at table_offset(NS).
+constexpr int table_offset(int ns) { return ns == 8 ? 0 : ns == 64 ? 7 * 8 : 7 * 72; }
+inline int table_entries(int n)
 {
-    constexpr int T = N / 8;          // threads
-    constexpr int B = N / R / T;      // butterflies per thread
-    const int t = threadIdx.x;
-    double2 v[B][R];
-#pragma unroll
-    for (int b = 0; b < B; ++b) {
-        const int j = t + b * T;
-        const int k = j & (Ns - 1);
-#pragma unroll
-        for (int r = 0; r < R; ++r) v[b][r] = buf[j + r * (N / R)];
-        if (Ns > 1) {
-            const int step = N / (Ns * R);
-#pragma unroll
-            for (int r = 1; r < R; ++r) {
-                double2 w = W[r * k * step];
-                if (INV) w.y = -w.y;
-                v[b][r] = cmul(v[b][r], w);
-            }
-        }
-        dft<R, INV>(v[b]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int b = 0; b < B; ++b) {
-        const int j = t + b * T;
-        const int k = j & (Ns - 1);
-        const int base = (j - k) * R + k;
-#pragma unroll
-        for (int r = 0; r < R; ++r) buf[base + r * Ns] = v[b][r];
-    }
-    __syncthreads();
+    int e = 0;
+    for (int ns = 8; ns < n; ns *= 8) e += ((n / ns >= 8 ? 8 : n / ns) - 1) * ns;
+    return e;
 }
 
-// In-place N-point transform of buf by the whole block (blockDim.x == N / 8).
-// The caller synchronises the block after filling buf; the block is
-// synchronised on return.
-template <int N, bool INV>
-__device__ __forceinline__ void fft(double2 *buf, const double2 *__restrict__ W)
+// The butterflies of one pass on a thread's eight points: v[b + r B] is input
+// (and output) r of butterfly j = t + b T.
+template <int N, int NS, bool INV>
+__device__ __forceinline__ void butterflies(double2 v[8], int t, const double2 *__restrict__ W)
+{
+    constexpr int R = radix<N, NS>(), B = 8 / R, T = N / 8;
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        double2 x[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) x[r] = v[b + r * B];
+        if constexpr (NS > 1) {
+            const int k = (t + b * T) & (NS - 1);
+            const double2 *w0 = W + table_offset(NS) + k;
+#pragma unroll
+            for (int r = 1; r < R; ++r) {
+                double2 w = w0[(r - 1) * NS];
+                if (INV) w.y = -w.y;
+                x[r] = cmul(x[r], w);
+            }
+        }
+        dft<R, INV>(x);
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[b + r * B] = x[r];
+    }
+}
+
+// Who takes a transform: the whole block, or (BLOCK = false) a group of N / 8 <=
+// 64 threads inside one wave, whose LDS accesses are in order by themselves, so
+// that the blocks' barriers fall away.
+template <bool BLOCK>
+__device__ __forceinline__ void sync()
+{
+    if constexpr (BLOCK) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// The pass's outputs to LDS and the next pass's inputs back, synchronised
+// before the buffer is written and before it is read.
+template <int N, int NS, bool BLOCK>
+__device__ __forceinline__ void exchange(double2 v[8], int t, double2 *buf)
+{
+    constexpr int R = radix<N, NS>(), B = 8 / R, T = N / 8;
+    sync<BLOCK>();
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        const int j = t + b * T, k = j & (NS - 1), base = (j - k) * R + k;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            buf[pad(base) + r * (NS == 1 ? 1 : padded(NS))] = v[b + r * B];
+    }
+    sync<BLOCK>();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = buf[pad(t) + q * padded(T)];
+}
+
+// Zero, but not to the compiler.  Added to the index of what a transform loads,
+// it keeps a block that takes several transforms in a row from loading all
+// their inputs at once and from holding the twiddles of every pass in
+// registers from one to the next (250 registers and two waves per SIMD).
+__device__ __forceinline__ int opaque_zero()
+{
+    int z = 0;
+    asm volatile("" : "+s"(z) : : "memory");
+    return z;
+}
+
+// The values of v are formed here, not where they are used: a block that takes
+// several transforms in a row would otherwise carry the last pass's inputs and
+// twiddles of each into the next.
+__device__ __forceinline__ void settle(double2 v[8])
+{
+#pragma unroll
+    for (int q = 0; q < 8; ++q) asm volatile("" : "+v"(v[q].x), "+v"(v[q].y));
+}
+
+// N-point transform by N / 8 threads (see sync; t: the thread's number among
+// them): v[q] is point t + q N / 8 on entry and on return.  buf
+// (lds_entries<N>()) is written after a synchronisation, and may still be read
+// by other threads on return.
+template <int N, bool INV, bool BLOCK = true>
+__device__ __forceinline__ void fft(double2 v[8], int t, double2 *buf,
+                                    const double2 *__restrict__ W)
 {
     static_assert(N >= 64 && N <= 4096 && (N & (N - 1)) == 0, "built-in transform sizes");
-    pass<N, 8, INV>(buf, 1, W);
-    pass<N, 8, INV>(buf, 8, W);
-    if constexpr (N == 128) pass<N, 2, INV>(buf, 64, W);
-    if constexpr (N == 256) pass<N, 4, INV>(buf, 64, W);
-    if constexpr (N >= 512) pass<N, 8, INV>(buf, 64, W);
-    if constexpr (N == 1024) pass<N, 2, INV>(buf, 512, W);
-    if constexpr (N == 2048) pass<N, 4, INV>(buf, 512, W);
-    if constexpr (N == 4096) pass<N, 8, INV>(buf, 512, W);
+    static_assert(BLOCK || N <= 512, "a group stays inside a wave");
+    W += opaque_zero();
+    butterflies<N, 1, INV>(v, t, W);
+    exchange<N, 1, BLOCK>(v, t, buf);
+    butterflies<N, 8, INV>(v, t, W);
+    if constexpr (N > 64) {
+        exchange<N, 8, BLOCK>(v, t, buf);
+        butterflies<N, 64, INV>(v, t, W);
+    }
+    if constexpr (N > 512) {
+        exchange<N, 64, BLOCK>(v, t, buf);
+        butterflies<N, 512, INV>(v, t, W);
+    }
 }
 
 }  // namespace ns_fft

@@ -19,20 +19,20 @@
 // For every power of two n from 64 to 4096 (the default) the built-in
 // transforms (fft_lds.h) replace the library's (which stay available as an
 // explicit cross-check, and for other n) and fuse with the pointwise work,
-// in four kernels a step
 // over a transposed spectral layout (entry (row jy, column ix) of a
 // half-plane spectrum at ix * n + jy, so that every column is contiguous)
-// that holds only the columns inside the 2/3 band:
-//   a. fwd_rows_kernel: the grid product of a slab of rows, two real rows
-//      packed into one complex transform along x, unpacked into two half
-//      spectra;
-//   b. column_fwd_kernel: per band column, the transform along y, the band
+// that holds only the columns inside the 2/3 band.  A step starts from the
+// x-transformed advection term of the current level:
+//   a. column_fwd_kernel: per band column, its transform along y, the band
 //      and the AB2 update; column_emit_kernel: per band column and field,
-//      the field's values and its inverse transform along y;
-//   c. inv_rows_kernel: two rows of each field packed into one complex
-//      inverse transform along x (Hermitian extension), written as grid rows.
-// Each spectral array is read and written once per step and the grid
-// advection term never reaches HBM.
+//      the field's values and its inverse transform along y (up to n = 512
+//      one kernel does both, column_step_kernel);
+//   b. rows_kernel: per pair of grid rows, the four fields' inverse transforms
+//      along x (two real rows packed into one complex transform, Hermitian
+//      extension), their product u dw/dx + v dw/dy, and its forward transform
+//      along x, unpacked into two half spectra: the next step's start.  The
+//      grid holds the velocity only, written by a call's last step.
+// The vorticity's gradient and the advection term never reach HBM on the grid.
 #include <hip/hip_runtime.h>
 #include <hipfft/hipfft.h>
 
@@ -40,6 +40,7 @@
 #include <cstdio>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "fft_lds.h"
@@ -155,19 +156,6 @@ __global__ __launch_bounds__(kBlock) void scaled_kernel(const double2 *__restric
 
 // ---- built-in transform path (n = 64, 128, ..., 4096) ---------------------
 
-// Grid rows per row-pass block: four (two packed complex rows, 2N entries of
-// LDS) at N = 2048, two (one packed row) elsewhere: below 2048 twice as many
-// blocks fill the chip better (measured: 1024^2 step 71.9 -> 61.1 us; 2048^2
-// step 163 -> 167 us with two), and at 4096 one packed row is 64 KiB of LDS.
-template <int N>
-constexpr int rows_per_block() { return N == 2048 ? 4 : 2; }
-
-// Inverse row pass: one block per field and slab (1024^2 step 56.1 -> 52.3
-// us, 512^2 33.1 -> 30.7 us), except at 2048, where one block per slab walks
-// the four fields (161 us a step against 185 with a block per field).
-template <int N>
-constexpr bool field_blocks() { return N != 2048; }
-
 // Contiguous logical block ranges per XCD (workgroups go to the eight XCDs
 // round-robin): XCD x = b mod 8 takes logical blocks [x G/8, (x+1) G/8) up to
 // the remainder, so consecutive logical blocks share an L2.
@@ -177,208 +165,354 @@ __device__ __forceinline__ int xcd_block(int b, int G)
     return x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
 }
 
-// Row slab of a row-pass block.  Workgroups go to the eight XCDs round-robin;
-// XCD x takes the contiguous slabs [x G/8, (x+1) G/8) (G = N / rows per
-// block, a multiple of 8 for every built-in size), so the two slabs that share each
-// 128-byte line of a transposed column run on one XCD and share its L2.
-template <int N>
-__device__ __forceinline__ int row_slab()
-{
-    constexpr int G = N / rows_per_block<N>();
-    static_assert(G % 8 == 0, "slabs split evenly over the XCDs");
-    return (int)(blockIdx.x % 8) * (G / 8) + (int)(blockIdx.x / 8);
-}
-
 // Columns ix = 0 .. band_cols(N) - 1 are the ones with 3 ix < N.  Every other
 // column of the band-limited state, of the four fields and of the read-back
 // fields is zero, so the built-in path neither transforms nor stores it:
 // the row passes skip it and the inverse row pass supplies the zeros.
 constexpr int band_cols(int N) { return (N - 1) / 3 + 1; }
 
-// One slab of rows (rows_per_block) of the advection term (PRODUCT: u dw/dx + v dw/dy from the
-// four grid fields at g) or of one grid field (g), transformed along x:
-// rows (a, b) form z = a + i b, Z = FFT(z), and the half spectra are
-// A(k) = (Z(k) + conj Z(-k)) / 2, B(k) = (Z(k) - conj Z(-k)) / (2i).
-template <int N, bool PRODUCT>
-__global__ __launch_bounds__(N / 8) void fwd_rows_kernel(const double *__restrict__ g,
-                                                        double2 *__restrict__ specT,
-                                                        const double2 *__restrict__ W)
+// Columns of the band a thread of a row pass takes: k = t + c N / 8.
+template <int N>
+constexpr int cols_per_thread() { return (band_cols(N) + N / 8 - 1) / (N / 8); }
+
+// Two grid rows a, b transformed along x as z = a + i b (v[q] is point t + q N
+// / 8), unpacked into their half spectra A(k) = (Z(k) + conj Z(-k)) / 2,
+// B(k) = (Z(k) - conj Z(-k)) / (2i) at rows jy0 and jy0 + 1 of specT.
+template <int N, bool BLOCK = true>
+__device__ __forceinline__ void rows_forward(double2 v[8], int t, double2 *buf,
+                                             double2 *__restrict__ specT, int jy0,
+                                             const double2 *__restrict__ W)
 {
-    extern __shared__ double2 lds_rows[];   // kPairs packed rows of N entries
-    constexpr int T = N / 8;
-    constexpr size_t cells = (size_t)N * N;
-    constexpr int kPairs = rows_per_block<N>() / 2;
-    const int jy0 = row_slab<N>() * rows_per_block<N>();
-    for (int p = 0; p < kPairs; ++p) {
-        double2 *buf = lds_rows + p * N;
-        const double *ra = g + (size_t)(jy0 + 2 * p) * N;
-        const double *rb = ra + N;
-        for (int x = threadIdx.x; x < N; x += T) {
-            double a, b;
-            if constexpr (PRODUCT) {
-                a = ra[x] * ra[x + 2 * cells] + ra[x + cells] * ra[x + 3 * cells];
-                b = rb[x] * rb[x + 2 * cells] + rb[x + cells] * rb[x + 3 * cells];
-            } else {
-                a = ra[x];
-                b = rb[x];
-            }
-            buf[x] = make_double2(a, b);
-        }
-    }
-    __syncthreads();
-    for (int p = 0; p < kPairs; ++p) ns_fft::fft<N, false>(lds_rows + p * N, W);
-    constexpr int KB = band_cols(N);
-    for (int e = threadIdx.x; e < kPairs * KB; e += T) {
-        const int k = e / kPairs, p = e % kPairs;
-        const double2 *buf = lds_rows + p * N;
-        const double2 z = buf[k], zc = buf[(N - k) & (N - 1)];
-        double2 *dst = specT + (size_t)k * N + jy0 + 2 * p;
+    constexpr int T = N / 8, KB = band_cols(N);
+    ns_fft::fft<N, false, BLOCK>(v, t, buf, W);
+    ns_fft::sync<BLOCK>();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) buf[ns_fft::pad(t) + q * ns_fft::padded(T)] = v[q];
+    ns_fft::sync<BLOCK>();
+#pragma unroll
+    for (int c = 0; c < cols_per_thread<N>(); ++c) {
+        const int k = t + c * T;
+        if (k >= KB) break;
+        // entry -k is N - k, and entry 0 for k = 0
+        const double2 z = buf[ns_fft::pad(t) + c * ns_fft::padded(T)];
+        const double2 zc = k == 0 ? z : buf[ns_fft::pad(N - t) - c * ns_fft::padded(T)];
+        double2 *dst = specT + (size_t)k * N + jy0;
         dst[0] = make_double2(0.5 * (z.x + zc.x), 0.5 * (z.y - zc.y));
         dst[1] = make_double2(0.5 * (z.y + zc.y), -0.5 * (z.x - zc.x));
     }
 }
 
+// Rows jy0 and jy0 + 1 of one field (a plane of the transposed spectra, already
+// transformed along y) back to the grid: Z(k) = A(k) + i B(k) and Z(N-k) =
+// conj A(k) + i conj B(k) for the band columns (the imaginary parts at k = 0
+// dropped as in any complex-to-real transform), zero elsewhere; z = IFFT(Z)
+// has a = Re z, b = Im z, v[q] at point t + q N / 8.
+template <int N, bool BLOCK = true>
+__device__ __forceinline__ void rows_inverse(double2 v[8], int t, double2 *buf,
+                                             const double2 *__restrict__ field, int jy0,
+                                             const double2 *__restrict__ W)
+{
+    constexpr int T = N / 8, KB = band_cols(N), C = cols_per_thread<N>();
+    field += ns_fft::opaque_zero();
+    double2 A[C], B[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int k = t + c * T;
+        A[c] = B[c] = make_double2(0.0, 0.0);
+        if (k < KB) {
+            const double2 *sp = field + (size_t)k * N + jy0;
+            A[c] = sp[0];
+            B[c] = sp[1];
+        }
+    }
+    ns_fft::sync<BLOCK>();   // the buffer's last readers are done
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int k = t + c * T;
+        if (k >= KB) break;
+        if (k == 0) A[c].y = B[c].y = 0.0;
+        buf[ns_fft::pad(t) + c * ns_fft::padded(T)] =
+            make_double2(A[c].x - B[c].y, A[c].y + B[c].x);
+        if (k > 0)
+            buf[ns_fft::pad(N - t) - c * ns_fft::padded(T)] =
+                make_double2(A[c].x + B[c].y, B[c].x - A[c].y);
+    }
+    ns_fft::sync<BLOCK>();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int i = t + q * T;
+        v[q] = i >= KB && i <= N - KB ? make_double2(0.0, 0.0)
+                                      : buf[ns_fft::pad(t) + q * ns_fft::padded(T)];
+    }
+    ns_fft::fft<N, true, BLOCK>(v, t, buf, W);
+    ns_fft::settle(v);
+}
+
+template <int N>
+__device__ __forceinline__ void store_rows(const double2 v[8], int t, double *__restrict__ grid,
+                                           int jy0)
+{
+    constexpr int T = N / 8;
+    double *ra = grid + (size_t)jy0 * N + t;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        ra[q * T] = v[q].x;
+        ra[q * T + N] = v[q].y;
+    }
+}
+
+// The x-transform of one grid field g.  Blocks take pairs of rows in XCD order
+// (the four pairs that share each 128-byte line of a transposed column run on
+// one XCD and share its L2), as in the row passes below.
+template <int N>
+__global__ __launch_bounds__(N / 8) void fwd_rows_kernel(const double *__restrict__ g,
+                                                        double2 *__restrict__ specT,
+                                                        const double2 *__restrict__ W)
+{
+    extern __shared__ double2 lds_rows[];
+    constexpr int T = N / 8;
+    const int jy0 = 2 * xcd_block(blockIdx.x, N / 2);
+    const double *ra = g + (size_t)jy0 * N;
+    double2 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        v[q] = make_double2(ra[threadIdx.x + q * T], ra[threadIdx.x + q * T + N]);
+    rows_forward<N>(v, threadIdx.x, lds_rows, specT, jy0, W);
+}
+
+// One field back to the grid (read-back of omega or psi).
+template <int N>
+__global__ __launch_bounds__(N / 8) void inv_rows_kernel(const double2 *__restrict__ field,
+                                                        double *__restrict__ grid,
+                                                        const double2 *__restrict__ W)
+{
+    extern __shared__ double2 lds_rows[];
+    const int jy0 = 2 * xcd_block(blockIdx.x, N / 2);
+    double2 v[8];
+    rows_inverse<N>(v, threadIdx.x, lds_rows, field, jy0, W);
+    store_rows<N>(v, threadIdx.x, grid, jy0);
+}
+
+// One pair of rows from the four fields' column transforms to the x-transform
+// of the advection term u dw/dx + v dw/dy.  STORE: the velocity goes to the
+// grid too (u, then v).  Bound by the latency of its five transforms in a row,
+// so by the waves resident: registers are held to four per SIMD (124; see
+// opaque_zero and settle), which at N = 2048 makes all 1024 blocks resident at
+// once.
+template <int N, bool STORE>
+__global__ __launch_bounds__(N / 8) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void rows_kernel(const double2 *__restrict__ fields, size_t plane, double *__restrict__ grid,
+                 double2 *__restrict__ specT, const double2 *__restrict__ W)
+{
+    extern __shared__ double2 lds_rows[];
+    constexpr size_t cells = (size_t)N * N;
+    const int jy0 = 2 * xcd_block(blockIdx.x, N / 2), t = threadIdx.x;
+    double2 a[8], b[8], p[8];
+    rows_inverse<N>(a, t, lds_rows, fields, jy0, W);               // u
+    if (STORE) store_rows<N>(a, t, grid, jy0);
+    rows_inverse<N>(b, t, lds_rows, fields + 2 * plane, jy0, W);   // dw/dx
+#pragma unroll
+    for (int q = 0; q < 8; ++q) p[q] = make_double2(a[q].x * b[q].x, a[q].y * b[q].y);
+    ns_fft::settle(p);
+    rows_inverse<N>(a, t, lds_rows, fields + plane, jy0, W);       // v
+    if (STORE) store_rows<N>(a, t, grid + cells, jy0);
+    rows_inverse<N>(b, t, lds_rows, fields + 3 * plane, jy0, W);   // dw/dy
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        p[q] = make_double2(fma(a[q].x, b[q].x, p[q].x), fma(a[q].y, b[q].y, p[q].y));
+    rows_forward<N>(p, t, lds_rows, specT, jy0, W);
+}
+
+// rows_kernel for small grids, whose few blocks leave the chip idle: the four
+// fields' transforms side by side, by four groups of N / 8 threads each inside
+// one wave, then the product and its transform by the first group.  Two
+// transforms in a row instead of five, without barriers.
+template <int N, bool STORE>
+__global__ __launch_bounds__(N / 2) void rows_small_kernel(const double2 *__restrict__ fields,
+                                                          size_t plane, double *__restrict__ grid,
+                                                          double2 *__restrict__ specT,
+                                                          const double2 *__restrict__ W)
+{
+    extern __shared__ double2 lds_rows[];   // a buffer per field
+    constexpr int T = N / 8, E = ns_fft::lds_entries<N>();
+    const int jy0 = 2 * xcd_block(blockIdx.x, N / 2);
+    const int f = threadIdx.x / T, t = threadIdx.x % T;
+    double2 *buf = lds_rows + f * E;
+    double2 v[8];
+    rows_inverse<N, false>(v, t, buf, fields + f * plane, jy0, W);
+    if (STORE && f < 2) store_rows<N>(v, t, grid + f * ((size_t)N * N), jy0);
+    ns_fft::sync<false>();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) buf[ns_fft::pad(t) + q * ns_fft::padded(T)] = v[q];
+    __syncthreads();
+    if (f > 0) return;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const double2 *b = buf + ns_fft::pad(t) + q * ns_fft::padded(T);
+        const double2 y = b[E], wx = b[2 * E], wy = b[3 * E];
+        v[q] = make_double2(fma(y.x, wy.x, v[q].x * wx.x), fma(y.y, wy.y, v[q].y * wx.y));
+    }
+    rows_forward<N, false>(v, t, buf, specT, jy0, W);
+}
+
 enum ColumnMode { kColInit = 0, kColFirst = 1, kColStep = 2 };
 
+// The new state of one mode from the transform Nh of the advection term: the
+// band, the right-hand side and AB2 (MODE init: Nh is the vorticity).
+template <int N, int MODE>
+__device__ __forceinline__ void advance_mode(double2 Nh, int ix, int jy, const Spec &S,
+                                             const double2 *w_hat, const double2 *r_prev,
+                                             size_t idx, double2 &w_new, double2 &r)
+{
+    const int my = signed_mode(jy, N);
+    if (!in_band(ix, my, N)) Nh = make_double2(0.0, 0.0);
+    if constexpr (MODE == kColInit) {
+        w_new = Nh;
+        r = make_double2(0.0, 0.0);
+    } else {
+        const double kx = S.kscale * ix, ky = S.kscale * my;
+        const double visc = S.nu * (kx * kx + ky * ky);
+        const double2 w = w_hat[idx];
+        r = make_double2(-Nh.x - visc * w.x, -Nh.y - visc * w.y);
+        const double2 r_old = MODE == kColFirst ? r : r_prev[idx];
+        w_new = make_double2(w.x + S.dt * (1.5 * r.x - 0.5 * r_old.x),
+                             w.y + S.dt * (1.5 * r.y - 0.5 * r_old.y));
+    }
+}
+
+// Value of one field at one mode of vorticity w, scaled by 1/n^2: u = i k_y
+// psi, v = -i k_x psi, dw/dx = i k_x w, dw/dy = i k_y w, or omega or psi.
+enum Field { kU = 0, kV = 1, kWx = 2, kWy = 3, kOmega = 4, kPsi = 5 };
+
+__device__ __forceinline__ double2 field_mode(int f, double2 w, double kx, double ky, double s)
+{
+    if (f == kU || f == kV || f == kPsi) {
+        const double k2 = kx * kx + ky * ky;
+        double2 p = make_double2(0.0, 0.0);
+        if (k2 > 0.0) p = make_double2(w.x / k2, w.y / k2);
+        if (f == kU) return make_double2(-ky * p.y * s, ky * p.x * s);
+        if (f == kV) return make_double2(kx * p.y * s, -kx * p.x * s);
+        return make_double2(p.x * s, p.y * s);
+    }
+    if (f == kWx) return make_double2(-kx * w.y * s, kx * w.x * s);
+    if (f == kWy) return make_double2(-ky * w.y * s, ky * w.x * s);
+    return make_double2(w.x * s, w.y * s);
+}
+
 // Column ix < band_cols(N) of the transposed spectra, one block per column:
-// plane 0 of `fields` (the x-transformed rows) transformed along y, the band
-// taken, and the state stored (init) or advanced by AB2 (step).
+// the x-transformed rows at specT transformed along y, the band taken, and
+// the state stored (init) or advanced by AB2 (step).
 template <int N, int MODE>
 __global__ __launch_bounds__(N / 8) void column_fwd_kernel(double2 *__restrict__ w_hat,
                                                           double2 *__restrict__ r_prev,
-                                                          const double2 *__restrict__ fields,
+                                                          const double2 *__restrict__ specT,
                                                           Spec S, const double2 *__restrict__ W)
 {
-    extern __shared__ double2 lds_col[];   // N entries
+    extern __shared__ double2 lds_col[];
     constexpr int T = N / 8;
     const int ix = blockIdx.x, t = threadIdx.x;
     const size_t col = (size_t)ix * N;
-    const double kx = S.kscale * ix;
+    double2 v[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) lds_col[t + q * T] = fields[col + t + q * T];
-    __syncthreads();
-    ns_fft::fft<N, false>(lds_col, W);
+    for (int q = 0; q < 8; ++q) v[q] = specT[col + t + q * T];
+    ns_fft::fft<N, false>(v, t, lds_col, W);
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-        const int jy = t + q * T;
-        const size_t idx = col + jy;
-        const int my = signed_mode(jy, N);
-        const double2 Nh = in_band(ix, my, N) ? lds_col[jy] : make_double2(0.0, 0.0);
-        if constexpr (MODE == kColInit) {
-            w_hat[idx] = Nh;
-        } else {
-            const double ky = S.kscale * my;
-            const double visc = S.nu * (kx * kx + ky * ky);
-            const double2 w = w_hat[idx];
-            const double2 r = make_double2(-Nh.x - visc * w.x, -Nh.y - visc * w.y);
-            const double2 r_old = MODE == kColFirst ? r : r_prev[idx];
-            w_hat[idx] = make_double2(w.x + S.dt * (1.5 * r.x - 0.5 * r_old.x),
-                                      w.y + S.dt * (1.5 * r.y - 0.5 * r_old.y));
-            r_prev[idx] = r;
-        }
+        const size_t idx = col + t + q * T;
+        double2 w, r;
+        advance_mode<N, MODE>(v[q], ix, t + q * T, S, w_hat, r_prev, idx, w, r);
+        w_hat[idx] = w;
+        if (MODE != kColInit) r_prev[idx] = r;
     }
 }
 
-enum EmitMode { kEmitFields = 0, kEmitW = 1, kEmitPsi = 2 };
-
 // One field of one band column, transformed back along y: the four fields
-// u = i k_y psi, v = -i k_x psi, dw/dx = i k_x w, dw/dy = i k_y w (emit
-// mode), or omega or psi alone (read-back modes), each scaled by 1/n^2.
-// Logical block l = column * nf + field, so a column's fields run on one XCD
-// and re-read its state from that L2.
-template <int N, int MODE>
+// (nf = 4, plane f each) or one (nf = 1).  Logical block l = column * nf +
+// field, so a column's fields run on one XCD and re-read its state from that
+// L2.
+template <int N>
 __global__ __launch_bounds__(N / 8) void column_emit_kernel(const double2 *__restrict__ w_hat,
-                                                           double2 *__restrict__ fields, Spec S,
+                                                           double2 *__restrict__ fields, int f0,
+                                                           int nf, Spec S,
                                                            const double2 *__restrict__ W)
 {
-    extern __shared__ double2 lds_col[];   // N entries
+    extern __shared__ double2 lds_col[];
     constexpr int T = N / 8;
-    constexpr int nf = MODE == kEmitFields ? 4 : 1;
     const int l = xcd_block(blockIdx.x, band_cols(N) * nf);
     const int ix = l / nf, f = l % nf, t = threadIdx.x;
     const size_t col = (size_t)ix * N;
-    const double kx = S.kscale * ix, s = S.inv_nn;
+    double2 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = w_hat[col + t + q * T];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        v[q] = field_mode(f0 + f, v[q], S.kscale * ix, S.kscale * signed_mode(t + q * T, N),
+                          S.inv_nn);
+    ns_fft::fft<N, true>(v, t, lds_col, W);
+    double2 *dst = fields + (size_t)f * S.plane + col;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) dst[t + q * T] = v[q];
+}
+
+// column_fwd_kernel and column_emit_kernel of a step in one, for small grids:
+// the four blocks of a column each advance its state (the first one stores it,
+// into the other buffer: the rest may still be reading the old one) and take
+// one field back along y.  One launch and one trip through memory less for
+// three more transforms of a column.
+template <int N, int MODE>
+__global__ __launch_bounds__(N / 8) void column_step_kernel(
+    const double2 *__restrict__ w_hat, const double2 *__restrict__ r_prev,
+    double2 *__restrict__ w_out, double2 *__restrict__ r_out, const double2 *__restrict__ specT,
+    double2 *__restrict__ fields, Spec S, const double2 *__restrict__ W)
+{
+    extern __shared__ double2 lds_col[];
+    constexpr int T = N / 8;
+    const int l = xcd_block(blockIdx.x, band_cols(N) * 4);
+    const int ix = l / 4, f = l % 4, t = threadIdx.x;
+    const size_t col = (size_t)ix * N;
+    double2 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = specT[col + t + q * T];
+    ns_fft::fft<N, false>(v, t, lds_col, W);
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const int jy = t + q * T;
-        const double ky = S.kscale * signed_mode(jy, N);
-        const double k2 = kx * kx + ky * ky;
-        const double2 w = w_hat[col + jy];
-        double2 p = make_double2(0.0, 0.0);
-        if (k2 > 0.0) p = make_double2(w.x / k2, w.y / k2);
-        double2 v;
-        if constexpr (MODE == kEmitW) v = make_double2(w.x * s, w.y * s);
-        else if constexpr (MODE == kEmitPsi) v = make_double2(p.x * s, p.y * s);
-        else if (f == 0) v = make_double2(-ky * p.y * s, ky * p.x * s);    // u  =  i k_y psi
-        else if (f == 1) v = make_double2(kx * p.y * s, -kx * p.x * s);    // v  = -i k_x psi
-        else if (f == 2) v = make_double2(-kx * w.y * s, kx * w.x * s);    // dw/dx
-        else v = make_double2(-ky * w.y * s, ky * w.x * s);                // dw/dy
-        lds_col[jy] = v;
+        double2 w, r;
+        advance_mode<N, MODE>(v[q], ix, jy, S, w_hat, r_prev, col + jy, w, r);
+        if (f == 0) {
+            w_out[col + jy] = w;
+            r_out[col + jy] = r;
+        }
+        v[q] = field_mode(f, w, S.kscale * ix, S.kscale * signed_mode(jy, N), S.inv_nn);
     }
-    __syncthreads();
-    ns_fft::fft<N, true>(lds_col, W);
+    ns_fft::fft<N, true>(v, t, lds_col, W);
     double2 *dst = fields + (size_t)f * S.plane + col;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) dst[t + q * T] = lds_col[t + q * T];
+    for (int q = 0; q < 8; ++q) dst[t + q * T] = v[q];
 }
 
-// One slab of rows (rows_per_block) of one or all nf fields (planes of the
-// transposed spectra, already transformed along y; see field_blocks) back
-// to the grid: rows (a, b) of a field form
-// Z(k) = A(k) + i B(k) and Z(N-k) = conj A(k) + i conj B(k) for the band
-// columns k < KB (the imaginary parts at k = 0 dropped as in any
-// complex-to-real transform) and zero elsewhere; z = IFFT(Z) gives a = Re z,
-// b = Im z.
+// Grids up to kSmallGrid take rows_small_kernel (a group of N / 8 threads has to
+// stay inside a wave), up to kColumnStep column_step_kernel.  Us a step with the
+// general kernels and with these: n = 64 12.6 / 9.3, 256 15.4 / 11.6, 512 (both)
+// 24 / 16.4; 1024 (column_step_kernel) 41.0 / 39.1.  At 2048 its extra
+// transforms would cost three times column_fwd_kernel's 20 us.
+constexpr int kSmallGrid = 512, kColumnStep = 1024;
+
 template <int N>
-__global__ __launch_bounds__(N / 8) void inv_rows_kernel(const double2 *__restrict__ fields,
-                                                        double *__restrict__ grid, int nf,
-                                                        size_t plane,
-                                                        const double2 *__restrict__ W)
+void launch_rows(bool store, const double2 *fields, size_t plane, double *grid, double2 *adv,
+                 const double2 *W, hipStream_t st)
 {
-    extern __shared__ double2 lds_rows[];   // kPairs packed rows of N entries
-    constexpr int T = N / 8, KB = band_cols(N);
-    constexpr int kPairs = rows_per_block<N>() / 2, G = N / rows_per_block<N>();
-    constexpr size_t cells = (size_t)N * N;
-    int f0, f1, jy0;
-    if constexpr (field_blocks<N>()) {
-        // one block per (field, slab); a field's adjacent slabs share an XCD
-        const int l = xcd_block(blockIdx.x, nf * G);
-        f0 = l / G;
-        f1 = f0 + 1;
-        jy0 = (l % G) * rows_per_block<N>();
+    const size_t lds = (size_t)ns_fft::lds_entries<N>() * sizeof(double2);
+    if constexpr (N <= kSmallGrid) {
+        if (store)
+            rows_small_kernel<N, true><<<N / 2, N / 2, 4 * lds, st>>>(fields, plane, grid, adv, W);
+        else
+            rows_small_kernel<N, false><<<N / 2, N / 2, 4 * lds, st>>>(fields, plane, grid, adv, W);
     } else {
-        f0 = 0;
-        f1 = nf;
-        jy0 = row_slab<N>() * rows_per_block<N>();
-    }
-    for (int f = f0; f < f1; ++f) {
-        const double2 *src = fields + (size_t)f * plane;
-        for (int e = threadIdx.x; e < kPairs * KB; e += T) {
-            const int k = e / kPairs, p = e % kPairs;
-            const double2 *sp = src + (size_t)k * N + jy0 + 2 * p;
-            double2 A = sp[0], B = sp[1];
-            if (k == 0) {
-                A.y = 0.0;
-                B.y = 0.0;
-            }
-            double2 *buf = lds_rows + p * N;
-            buf[k] = make_double2(A.x - B.y, A.y + B.x);
-            if (k > 0) buf[N - k] = make_double2(A.x + B.y, B.x - A.y);
-        }
-        // columns KB .. N/2 and their mirrors N/2 .. N-KB are zero
-        for (int x = KB + threadIdx.x; x <= N - KB; x += T)
-            for (int p = 0; p < kPairs; ++p) lds_rows[p * N + x] = make_double2(0.0, 0.0);
-        __syncthreads();
-        for (int p = 0; p < kPairs; ++p) ns_fft::fft<N, true>(lds_rows + p * N, W);
-        for (int p = 0; p < kPairs; ++p) {
-            double *ra = grid + (size_t)f * cells + (size_t)(jy0 + 2 * p) * N;
-            for (int x = threadIdx.x; x < N; x += T) {
-                const double2 z = lds_rows[p * N + x];
-                ra[x] = z.x;
-                ra[x + N] = z.y;
-            }
-        }
-        __syncthreads();   // lds_rows is refilled for the next field
+        if (store)
+            rows_kernel<N, true><<<N / 2, N / 8, lds, st>>>(fields, plane, grid, adv, W);
+        else
+            rows_kernel<N, false><<<N / 2, N / 8, lds, st>>>(fields, plane, grid, adv, W);
     }
 }
 
@@ -389,13 +523,16 @@ struct ns2d_ctx {
     hipStream_t stream = nullptr;
     int n = 0, nh = 0;
     double L = 0, nu = 0, dt = 0;
+    double2 *spectra = nullptr;   // one allocation: the spectral planes that follow
     double2 *w_hat = nullptr, *r_prev = nullptr, *fields = nullptr;   // fields: 4 planes
-    double *grid = nullptr;   // 4 grid fields: u, v, dw/dx, dw/dy
+    double2 *w_next = nullptr, *r_next = nullptr;   // the other state (column_step_kernel)
+    double *grid = nullptr;   // 4 grid fields: u, v, dw/dx, dw/dy (built-in path: u, v and,
+                              // in place of the others, the x-transformed advection term)
     double *tmp = nullptr;    // grid scratch: advection term, read-back transforms
     hipfftHandle r2c = 0, c2r4 = 0, c2r1 = 0;
     bool r2c_ok = false, c2r4_ok = false, c2r1_ok = false;
     bool builtin = false;        // built-in transforms, transposed spectral layout
-    double2 *twiddle = nullptr;  // exp(-2 pi i m / n), m < n (built-in path)
+    double2 *twiddle = nullptr;  // the passes' twiddles (built-in path, see fft_lds.h)
     bool have_state = false, first = true;
     int64_t steps = 0;
     std::string err;
@@ -444,52 +581,57 @@ void release(ns2d_ctx *c)
     if (c->r2c_ok) hipfftDestroy(c->r2c);
     if (c->c2r4_ok) hipfftDestroy(c->c2r4);
     if (c->c2r1_ok) hipfftDestroy(c->c2r1);
-    if (c->w_hat) (void)hipFree(c->w_hat);
-    if (c->r_prev) (void)hipFree(c->r_prev);
-    if (c->fields) (void)hipFree(c->fields);
+    if (c->spectra) (void)hipFree(c->spectra);
     if (c->grid) (void)hipFree(c->grid);
     if (c->tmp) (void)hipFree(c->tmp);
     if (c->twiddle) (void)hipFree(c->twiddle);
 }
 
-enum BuiltinOp { kOpInit, kOpStep, kOpReadW, kOpReadPsi };
+// kOpStep: a step whose velocity nobody reads (not the last of a call)
+enum BuiltinOp { kOpInit, kOpStep, kOpLastStep, kOpReadW, kOpReadPsi };
 
 template <int N>
 ns2d_status run_builtin_n(ns2d_ctx *c, BuiltinOp op)
 {
     constexpr int T = N / 8;
-    constexpr int kPairs = rows_per_block<N>() / 2;
-    const size_t rows_lds = kPairs * (size_t)N * sizeof(double2);
-    const size_t col_lds = (size_t)N * sizeof(double2);
-    const dim3 rows_grid(N / rows_per_block<N>()), col_grid(band_cols(N));
+    const size_t lds = (size_t)ns_fft::lds_entries<N>() * sizeof(double2);
+    const dim3 rows(N / 2), cols(band_cols(N)), cols4(4 * band_cols(N));
     const Spec S = make_spec(c);
     hipStream_t st = c->stream;
     const double2 *Wt = c->twiddle;
-    const dim3 emit4_grid(4 * band_cols(N)), emit1_grid(band_cols(N));
-    const dim3 inv4_grid(field_blocks<N>() ? 4 * rows_grid.x : rows_grid.x);
+    double2 *adv = reinterpret_cast<double2 *>(c->grid + 2 * (size_t)N * N);
     switch (op) {
     case kOpInit:
-        fwd_rows_kernel<N, false><<<rows_grid, T, rows_lds, st>>>(c->tmp, c->fields, Wt);
-        column_fwd_kernel<N, kColInit><<<col_grid, T, col_lds, st>>>(c->w_hat, c->r_prev, c->fields, S, Wt);
-        column_emit_kernel<N, kEmitFields><<<emit4_grid, T, col_lds, st>>>(c->w_hat, c->fields, S, Wt);
-        inv_rows_kernel<N><<<inv4_grid, T, rows_lds, st>>>(c->fields, c->grid, 4, S.plane, Wt);
+        fwd_rows_kernel<N><<<rows, T, lds, st>>>(c->tmp, adv, Wt);
+        column_fwd_kernel<N, kColInit><<<cols, T, lds, st>>>(c->w_hat, c->r_prev, adv, S, Wt);
+        column_emit_kernel<N><<<cols4, T, lds, st>>>(c->w_hat, c->fields, kU, 4, S, Wt);
+        launch_rows<N>(true, c->fields, S.plane, c->grid, adv, Wt, st);
         break;
     case kOpStep:
-        fwd_rows_kernel<N, true><<<rows_grid, T, rows_lds, st>>>(c->grid, c->fields, Wt);
-        if (c->first)
-            column_fwd_kernel<N, kColFirst><<<col_grid, T, col_lds, st>>>(c->w_hat, c->r_prev, c->fields, S, Wt);
-        else
-            column_fwd_kernel<N, kColStep><<<col_grid, T, col_lds, st>>>(c->w_hat, c->r_prev, c->fields, S, Wt);
-        column_emit_kernel<N, kEmitFields><<<emit4_grid, T, col_lds, st>>>(c->w_hat, c->fields, S, Wt);
-        inv_rows_kernel<N><<<inv4_grid, T, rows_lds, st>>>(c->fields, c->grid, 4, S.plane, Wt);
+    case kOpLastStep:
+        if constexpr (N <= kColumnStep) {
+            if (c->first)
+                column_step_kernel<N, kColFirst><<<cols4, T, lds, st>>>(
+                    c->w_hat, c->r_prev, c->w_next, c->r_next, adv, c->fields, S, Wt);
+            else
+                column_step_kernel<N, kColStep><<<cols4, T, lds, st>>>(
+                    c->w_hat, c->r_prev, c->w_next, c->r_next, adv, c->fields, S, Wt);
+            std::swap(c->w_hat, c->w_next);
+            std::swap(c->r_prev, c->r_next);
+        } else {
+            if (c->first)
+                column_fwd_kernel<N, kColFirst><<<cols, T, lds, st>>>(c->w_hat, c->r_prev, adv, S, Wt);
+            else
+                column_fwd_kernel<N, kColStep><<<cols, T, lds, st>>>(c->w_hat, c->r_prev, adv, S, Wt);
+            column_emit_kernel<N><<<cols4, T, lds, st>>>(c->w_hat, c->fields, kU, 4, S, Wt);
+        }
+        launch_rows<N>(op == kOpLastStep, c->fields, S.plane, c->grid, adv, Wt, st);
         break;
     case kOpReadW:
     case kOpReadPsi:
-        if (op == kOpReadW)
-            column_emit_kernel<N, kEmitW><<<emit1_grid, T, col_lds, st>>>(c->w_hat, c->fields, S, Wt);
-        else
-            column_emit_kernel<N, kEmitPsi><<<emit1_grid, T, col_lds, st>>>(c->w_hat, c->fields, S, Wt);
-        inv_rows_kernel<N><<<rows_grid, T, rows_lds, st>>>(c->fields, c->tmp, 1, S.plane, Wt);
+        column_emit_kernel<N><<<cols, T, lds, st>>>(c->w_hat, c->fields,
+                                                    op == kOpReadW ? kOmega : kPsi, 1, S, Wt);
+        inv_rows_kernel<N><<<rows, T, lds, st>>>(c->fields, c->tmp, Wt);
         break;
     }
     NS_HIP(c, hipGetLastError());
@@ -559,29 +701,42 @@ ns2d_status ns2d_create(const ns2d_config *cfg, ns2d_ctx **out)
     };
     if (hipGetDevice(&c->device) != hipSuccess) return bail(NS2D_E_HIP);
     const size_t plane = (size_t)n * c->nh, cells = (size_t)n * n;
-    if (hipMalloc(&c->w_hat, plane * sizeof(double2)) != hipSuccess ||
-        hipMalloc(&c->r_prev, plane * sizeof(double2)) != hipSuccess ||
-        hipMalloc(&c->fields, 4 * plane * sizeof(double2)) != hipSuccess ||
+    const bool two_states = own && n <= kColumnStep;
+    if (hipMalloc(&c->spectra, (two_states ? 8 : 6) * plane * sizeof(double2)) != hipSuccess ||
         hipMalloc(&c->grid, 4 * cells * sizeof(double)) != hipSuccess ||
         hipMalloc(&c->tmp, cells * sizeof(double)) != hipSuccess) {
         (void)hipGetLastError();
         return bail(NS2D_E_NOMEM);
     }
-    // measured faster than hipFFT at the sizes compared (2048^2: 161 vs 337
-    // us a step; 1024^2: 53 vs 101; 512^2: 31 vs 43)
+    c->fields = c->spectra;
+    c->w_hat = c->spectra + 4 * plane;
+    c->r_prev = c->spectra + 5 * plane;
+    if (two_states) {
+        c->w_next = c->spectra + 6 * plane;
+        c->r_next = c->spectra + 7 * plane;
+    }
+    // measured faster than hipFFT at the sizes compared (2048^2: 98 vs 337
+    // us a step; 1024^2: 39 vs 101; 512^2: 16 vs 43)
     c->builtin = own;
     if (c->builtin) {
         // twiddles from the long-double cosine and sine, rounded once
-        std::vector<double2> w(n);
-        for (int m = 0; m < n; ++m) {
-            const long double a = 2.0L * 3.14159265358979323846264338327950288L * m / n;
-            w[m] = make_double2((double)cosl(a), (double)-sinl(a));
+        std::vector<double2> w((size_t)ns_fft::table_entries(n));
+        size_t e = 0;
+        for (int ns = 8; ns < n; ns *= 8) {
+            const int R = n / ns >= 8 ? 8 : n / ns;
+            for (int r = 1; r < R; ++r)
+                for (int k = 0; k < ns; ++k) {
+                    const long long m = (long long)r * k * (n / (ns * R));
+                    const long double a = 2.0L * 3.14159265358979323846264338327950288L * m / n;
+                    w[e++] = make_double2((double)cosl(a), (double)-sinl(a));
+                }
         }
-        if (hipMalloc(&c->twiddle, n * sizeof(double2)) != hipSuccess) {
+        if (hipMalloc(&c->twiddle, w.size() * sizeof(double2)) != hipSuccess) {
             (void)hipGetLastError();
             return bail(NS2D_E_NOMEM);
         }
-        if (hipMemcpy(c->twiddle, w.data(), n * sizeof(double2), hipMemcpyHostToDevice) != hipSuccess)
+        if (hipMemcpy(c->twiddle, w.data(), w.size() * sizeof(double2), hipMemcpyHostToDevice) !=
+            hipSuccess)
             return bail(NS2D_E_HIP);
         *out = c;
         return NS2D_OK;
@@ -663,7 +818,7 @@ ns2d_status ns2d_step(ns2d_ctx *c, int32_t count)
     const unsigned pgrid = (unsigned)(want < (size_t)cus * 16 ? want : (size_t)cus * 16);
     if (c->builtin) {
         for (int32_t s = 0; s < count; ++s) {
-            const ns2d_status st = run_builtin(c, kOpStep);
+            const ns2d_status st = run_builtin(c, s + 1 < count ? kOpStep : kOpLastStep);
             if (st != NS2D_OK) return st;
             c->first = false;
             ++c->steps;
@@ -714,8 +869,8 @@ ns2d_status ns2d_get_fields(ns2d_ctx *c, double *u, double *v, double *omega, do
     double *outs[2] = {omega, psi};
     for (int which = 0; which < 2; ++which) {
         if (!outs[which]) continue;
-        // plane 0 of the spectral fields is free between steps (the next
-        // step's forward transform rewrites it before it is read)
+        // plane 0 of the spectral fields is free between steps (the next step
+        // rewrites it before it is read)
         if (c->builtin) {
             if ((st = run_builtin(c, which == 0 ? kOpReadW : kOpReadPsi)) != NS2D_OK) return st;
         } else {
