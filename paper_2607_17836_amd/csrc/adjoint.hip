@@ -9,9 +9,10 @@
 // is only continuous, and its derivative is the one-sided one of the cell
 // that holds the point.
 //
-// One thread carries one particle's adjoint vector(s) backwards through one
-// step: it recomputes the four stage points from the step's start position
-// (read from the segment tape), then applies the chain rule through the RK4
+// One thread carries one particle's adjoint vector(s) backwards through a run
+// of steps: for each it recomputes the four stage points from the step's start
+// position (read from the segment tape), with the Jacobian of the interpolated
+// velocity from the same nodes, then applies the chain rule through the RK4
 // combine, the stage states and the interpolation.  Grid gradients are
 // scatter-added: by default with FP64 atomics (summation order, hence the
 // last bits, depends on scheduling); in the deterministic mode as exact
@@ -106,17 +107,19 @@ __device__ __forceinline__ Sten64<K> stencil64(int scheme, const Loc64 &l)
     return s;
 }
 
-// Spatial Jacobian J = [du/dx, du/dy, dv/dx, dv/dy] of the time-blended
-// interpolated velocity at a stencil, its K x K nodes read through N (the
-// LDS tile or the ghost-bordered records, so the stencil never wraps).
+// Time-blended interpolated velocity (u, v) at a stencil, in the operations of
+// the step kernel (bil64 and cub64), and its spatial Jacobian J = [du/dx,
+// du/dy, dv/dx, dv/dy], from one read of its K x K nodes through N (the LDS
+// tile or the ghost-bordered records, so the stencil never wraps).
 template <int K, typename Nodes>
-__device__ __forceinline__ void jacobian_nodes(const Nodes &N, const StepParams &P,
-                                               const Sten64<K> &s, double wa, double wb,
-                                               int smode, double J[4])
+__device__ __forceinline__ void eval_nodes(const Nodes &N, const StepParams &P,
+                                           const Sten64<K> &s, const Loc64 &loc, double wa,
+                                           double wb, int smode, double &u, double &v, double J[4])
 {
-    double ux = 0.0, uy = 0.0, vx = 0.0, vy = 0.0;
+    double ux = 0.0, uy = 0.0, vx = 0.0, vy = 0.0, su = 0.0, sv = 0.0;
     with_smode(smode, [&](auto mode) {
         constexpr int SM = decltype(mode)::value;
+        double nu[K][2], nv[K][2];   // K == 2: both rows
 #pragma unroll
         for (int b = 0; b < K; ++b) {
             double rux = 0.0, rvx = 0.0, ru = 0.0, rv = 0.0;
@@ -125,38 +128,54 @@ __device__ __forceinline__ void jacobian_nodes(const Nodes &N, const StepParams 
             for (int a = 0; a < K; ++a) raw[a] = N.template load<SM>(a, b);
 #pragma unroll
             for (int a = 0; a < K; ++a) {
-                double u, v;
-                raw[a].blend(wa, wb, u, v);
-                rux += s.dx[a] * u;
-                rvx += s.dx[a] * v;
-                ru += s.wx[a] * u;
-                rv += s.wx[a] * v;
+                double mu, mv;
+                raw[a].blend(wa, wb, mu, mv);
+                rux += s.dx[a] * mu;
+                rvx += s.dx[a] * mv;
+                ru += s.wx[a] * mu;
+                rv += s.wx[a] * mv;
+                if constexpr (K == 2) {
+                    nu[a][b] = mu;
+                    nv[a][b] = mv;
+                }
             }
             ux += s.wy[b] * rux;
             vx += s.wy[b] * rvx;
             uy += s.dy[b] * ru;
             vy += s.dy[b] * rv;
+            su += s.wy[b] * ru;
+            sv += s.wy[b] * rv;
+        }
+        if constexpr (K == 2) {
+            double w00, w10, w01, w11;
+            bilinear_weights(loc.xi, loc.eta, w00, w10, w01, w11);
+            su = w00 * nu[0][0] + w10 * nu[1][0] + w01 * nu[0][1] + w11 * nu[1][1];
+            sv = w00 * nv[0][0] + w10 * nv[1][0] + w01 * nv[0][1] + w11 * nv[1][1];
         }
     });
+    u = su;
+    v = sv;
     J[0] = ux * P.invh;
     J[1] = uy * P.invh;
     J[2] = vx * P.invh;
     J[3] = vy * P.invh;
 }
 
-// The Jacobian from the block's LDS tile when the stencil lies inside it,
-// else from global memory.
+// The same from the block's LDS tile when the stencil lies inside it, else
+// from global memory.
 template <int K>
-__device__ __forceinline__ void jacobian64(const Rec64 *__restrict__ rec0, const double2 *tile,
-                                           const Tile &T, const StepParams &P, const Sten64<K> &s,
-                                           double wa, double wb, int smode, double J[4])
+__device__ __forceinline__ void eval_stencil(const Rec64 *__restrict__ rec0, const double2 *tile,
+                                             const Tile &T, const StepParams &P,
+                                             const Sten64<K> &s, const Loc64 &loc, double wa,
+                                             double wb, int smode, double &u, double &v,
+                                             double J[4])
 {
     int t;
     if (tile_index(T, s.i0, s.j0, K, P.n, P.mask, t))
-        jacobian_nodes<K>(TileNodes64{tile + t, T.w, T.w * T.h}, P, s, wa, wb, smode, J);
+        eval_nodes<K>(TileNodes64{(LdsPair64)tile + t, T.w, T.w * T.h}, P, s, loc, wa, wb, smode, u, v, J);
     else
-        jacobian_nodes<K>(RecNodes64{rec0 + (__mul24(s.j0, P.pitch) + s.i0), P.pitch}, P, s, wa,
-                          wb, smode, J);
+        eval_nodes<K>(RecNodes64{rec0 + (__mul24(s.j0, P.pitch) + s.i0), P.pitch}, P, s, loc, wa,
+                      wb, smode, u, v, J);
 }
 
 // Exact fixed-point form of a contribution c (|c| < 2^31): c ~ hi 2^-32 +
@@ -172,12 +191,37 @@ __device__ __forceinline__ void to_fixed(double c, unsigned long long &hi, unsig
     lo = (unsigned long long)((f - h) * 0x1p32);
 }
 
-__device__ __forceinline__ void add_fixed(unsigned long long *pair, double c)
+// Additions to LDS and to global memory.  Each is spelt with a pointer of its own
+// kind: a generic one would make them flat.
+typedef __attribute__((address_space(3))) double *LdsF64;
+typedef __attribute__((address_space(3))) unsigned long long *LdsU64;
+
+__device__ __forceinline__ void add_to(LdsF64 p, double c)
+{
+    (void)__hip_atomic_fetch_add(p, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void add_to(LdsU64 p, unsigned long long c)
+{
+    (void)__hip_atomic_fetch_add(p, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void add_to(double *p, double c)
+{
+    typedef __attribute__((address_space(1))) double *G;
+    (void)__hip_atomic_fetch_add((G)p, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void add_to(unsigned long long *p, unsigned long long c)
+{
+    typedef __attribute__((address_space(1))) unsigned long long *G;
+    (void)__hip_atomic_fetch_add((G)p, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <typename Ptr>
+__device__ __forceinline__ void add_fixed(Ptr pair, double c)
 {
     unsigned long long hi, lo;
     to_fixed(c, hi, lo);
-    atomicAdd(pair, hi);
-    atomicAdd(pair + 1, lo);
+    add_to(pair, hi);
+    add_to(pair + 1, lo);
 }
 
 // Accumulator of dL/d(grid) for one block.  gU in global memory is laid out
@@ -220,9 +264,9 @@ __device__ __forceinline__ void scatter64(const GridGrad<DET> &G, const StepPara
             const bool local = G.B.on && rx < G.B.w && ry < G.B.h;
             const int k = ry * G.B.w + rx;
             if (local && !DET) {
-                double *acc = static_cast<double *>(G.acc);
-                atomicAdd(acc + (2 * grp) * area + k, w * lx);
-                atomicAdd(acc + (2 * grp + 1) * area + k, w * ly);
+                const LdsF64 acc = (LdsF64)static_cast<double *>(G.acc);
+                add_to(acc + ((2 * grp) * area + k), w * lx);
+                add_to(acc + ((2 * grp + 1) * area + k), w * ly);
                 continue;
             }
 #pragma unroll
@@ -230,19 +274,70 @@ __device__ __forceinline__ void scatter64(const GridGrad<DET> &G, const StepPara
                 const double c = wt[sl] * w;
                 if (c == 0.0) continue;
                 if constexpr (DET) {
-                    unsigned long long *q =
-                        local ? static_cast<unsigned long long *>(G.acc) + 2 * ((2 * sl) * area + k)
-                              : static_cast<unsigned long long *>(G.gU) +
-                                    2 * ((2 * sl) * nn + (int64_t)j * n + i);
-                    const int64_t pl = local ? area : nn;   // plane stride
-                    add_fixed(q, c * lx);
-                    add_fixed(q + 2 * pl, c * ly);
+                    if (local) {
+                        const LdsU64 q = (LdsU64)static_cast<unsigned long long *>(G.acc) +
+                                         2 * ((2 * sl) * area + k);
+                        add_fixed(q, c * lx);
+                        add_fixed(q + 2 * area, c * ly);
+                    } else {
+                        unsigned long long *q = static_cast<unsigned long long *>(G.gU) +
+                                                2 * ((2 * sl) * nn + (int64_t)j * n + i);
+                        add_fixed(q, c * lx);
+                        add_fixed(q + 2 * nn, c * ly);
+                    }
                 } else {
-                    double *g = static_cast<double *>(G.gU);
-                    const int64_t kk = (int64_t)j * n + i;
-                    atomicAdd(g + (2 * sl) * nn + kk, c * lx);
-                    atomicAdd(g + (2 * sl + 1) * nn + kk, c * ly);
+                    double *g = static_cast<double *>(G.gU) + (int64_t)j * n + i;
+                    add_to(g + (2 * sl) * nn, c * lx);
+                    add_to(g + (2 * sl + 1) * nn, c * ly);
                 }
+            }
+        }
+    }
+}
+
+// The block's box to gU: one atomic per nonzero entry, the two slots' temporal
+// weights applied once per node.
+template <bool DET>
+__device__ __forceinline__ void flush_box(const GridGrad<DET> &G, const StepParams &P,
+                                          const StageWeights &W)
+{
+    const int n = P.n, area = G.B.w * G.B.h;
+    const int64_t nn = (int64_t)n * n;
+    for (int k = threadIdx.x; k < area; k += blockDim.x) {
+        const int ty = k / G.B.w, tx = k - ty * G.B.w;
+        int gx = G.B.x0 + tx, gy = G.B.y0 + ty;
+        gx -= gx >= n ? n : 0;
+        gy -= gy >= n ? n : 0;
+        const int64_t g = (int64_t)gy * n + gx;
+        if constexpr (DET) {
+            const LdsU64 acc = (LdsU64)static_cast<unsigned long long *>(G.acc);
+            unsigned long long *out = static_cast<unsigned long long *>(G.gU);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const unsigned long long hi = acc[2 * (q * area + k)];
+                const unsigned long long lo = acc[2 * (q * area + k) + 1];
+                if (hi | lo) {
+                    add_to(out + 2 * (q * nn + g), hi);
+                    add_to(out + 2 * (q * nn + g) + 1, lo);
+                }
+            }
+        } else {
+            const LdsF64 acc = (LdsF64)static_cast<double *>(G.acc);
+            double *out = static_cast<double *>(G.gU);
+            // time levels 0, 1, 2 were taken at the weights of stages 0, 1, 3
+            const double wa[3] = {W.wa[0], W.wa[1], W.wa[3]};
+            const double wb[3] = {W.wb[0], W.wb[1], W.wb[3]};
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+                for (int g3 = 0; g3 < 3; ++g3) {
+                    const double v = acc[(2 * g3 + c) * area + k];
+                    s0 += wa[g3] * v;
+                    s1 += wb[g3] * v;
+                }
+                if (s0 != 0.0) add_to(out + c * nn + g, s0);
+                if (s1 != 0.0) add_to(out + (2 + c) * nn + g, s1);
             }
         }
     }
@@ -254,13 +349,13 @@ __device__ __forceinline__ void add_jt(const double J[4], const double l[2], dou
     out[1] = J[1] * l[0] + J[3] * l[1];
 }
 
-// Recompute one step of every particle's position: out = wrap(in + step),
-// with the step kernel's LDS field tile of the block's box.
+// Positions of R.nsteps steps from `in`: tape[(k + 1) np + p] = wrap(position
+// after step k), with the step kernel's tile for each step; store_first: the
+// start positions go to tape[p] too.
 template <bool CUBIC>
-__global__ __launch_bounds__(kMaxBlock) void recompute64_kernel(StepParams P,
-                                                                const Rec64 *__restrict__ rec,
-                                                                const double2 *__restrict__ in,
-                                                                double2 *__restrict__ out)
+__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(CUBIC ? 4 : 6)))
+void recompute64_kernel(StepParams P, StepRun R, const Rec64 *__restrict__ rec, const double2 *in,
+                        double2 *tape, int64_t np, int store_first)
 {
     const int lb = blockIdx.x;
     const SpeciesDev &sp = P.sp[species_of(P, lb)];
@@ -269,50 +364,77 @@ __global__ __launch_bounds__(kMaxBlock) void recompute64_kernel(StepParams P,
     const bool active = local < sp.count;
     const int64_t p = sp.offset + local;
     const Rec64 *rec0 = rec + P.pitch + 1;
-    const double2 x = active ? in[p] : make_double2(0.0, 0.0);
-    Tile T = no_tile();
-    if (P.tile_cap > 0) {
-        const double2 a = in[sp.offset + base];
-        const int n = P.n, mask = P.mask;
-        const int ax = cell_of_floor(floor(a.x * P.invh), n, mask);
-        const int ay = cell_of_floor(floor(a.y * P.invh), n, mask);
-        const int cx = cell_of_floor(floor(x.x * P.invh), n, mask);
-        const int cy = cell_of_floor(floor(x.y * P.invh), n, mask);
-        int lo, hi;
-        stencil_reach(sp.scheme, lo, hi);
-        const int H = step_halo(P, sp.scheme, (float)P.dt);
-        const int64_t left = sp.count - base;
-        T = stage_tile<Rec64>(reinterpret_cast<Rec64 *>(lpt_dyn_lds), rec0, P, active, cx, cy, ax,
-                              ay, lo + H, hi + H,
-                              (int)(left < (int64_t)blockDim.x ? left : blockDim.x));
-    }
-    if (!active) return;
+    Rec64 *lds = reinterpret_cast<Rec64 *>(lpt_dyn_lds);
     const double2 *planes = reinterpret_cast<const double2 *>(lpt_dyn_lds);
-    double ddx, ddy;
-    if (!CUBIC || sp.scheme == kBilinear)
-        rk4_tracer64<false>(rec0, planes, T, P, P.w, sp.scheme, x, ddx, ddy);
-    else
-        rk4_tracer64<true>(rec0, planes, T, P, P.w, sp.scheme, x, ddx, ddy);
-    out[p] = make_double2(wrap_pos(x.x + ddx, P.L), wrap_pos(x.y + ddy, P.L));
+    double2 x = active ? in[p] : make_double2(0.0, 0.0);
+    if (active && store_first) tape[p] = x;
+    const double2 a0 = in[sp.offset + base];
+    int ax = cell_of_floor(floor(a0.x * P.invh), P.n, P.mask);
+    int ay = cell_of_floor(floor(a0.y * P.invh), P.n, P.mask);
+    for (int k = 0; k < R.nsteps; ++k) {
+        Tile T = no_tile();
+        if (P.tile_cap > 0) {
+            T = tile64(P, sp, lds, rec0, x, active, ax, ay, base);
+            ax = wrap_cell(T.x0 + T.w / 2, P.n, P.mask);
+            ay = wrap_cell(T.y0 + T.h / 2, P.n, P.mask);
+        }
+        if (!active) continue;
+        double ddx, ddy;
+        if (!CUBIC || sp.scheme == kBilinear)
+            rk4_tracer64<false>(rec0, planes, T, P, R.w[k], sp.scheme, x, ddx, ddy);
+        else
+            rk4_tracer64<true>(rec0, planes, T, P, R.w[k], sp.scheme, x, ddx, ddy);
+        x = make_double2(wrap_pos(x.x + ddx, P.L), wrap_pos(x.y + ddy, P.L));
+        tape[(k + 1) * np + p] = x;
+    }
 }
 
-// One reverse step.  lam holds NL adjoint vectors per particle
-// (lam[p * NL + r]); gU (may be null) receives the grid gradient of the
-// first one.  With AGG, the block first sums its contributions in an LDS box
-// of the grid (its particles' cells widened by the step's displacement
-// bound and the stencil reach; acc_cap nodes of LDS) and then adds the box
-// to gU with one atomic per nonzero entry; contributions outside the box
-// (particles faster than the bound, or a box beyond the LDS budget, which is
-// trimmed) go to gU directly.  DET: gU holds fixed-point pairs (see
-// to_fixed), and so does the box.
 extern __shared__ __align__(32) unsigned char adj_dyn_lds[];
 
-template <int NL, bool AGG, bool CUBIC, bool DET>
-__global__ __launch_bounds__(kMaxBlock) void adjoint64_kernel(StepParams P,
-                                                              const Rec64 *__restrict__ rec,
-                                                              const double2 *__restrict__ tape,
-                                                              double2 *__restrict__ lam,
-                                                              void *gU, int lds_bytes)
+// Box of the stencils of a block's stage points, for the gradient accumulators:
+// it holds every node they touch, unless that is more than `cap` nodes.  Then
+// it is cut down about its centre to a window that fits, or, beyond twice the
+// capacity, left out (B.on = 0): what falls outside goes to global memory.
+__device__ __forceinline__ Tile gradient_box(BoxAcc b, int ax, int ay, const StepParams &P, int lo,
+                                             int hi, int cap)
+{
+    const int n = P.n;
+    Tile B = block_box_reduce(b, ax, ay, n, P.mask, lo, hi);
+    B.w = min(B.w, n);
+    B.h = min(B.h, n);
+    B.on = B.w * B.h <= 2 * cap;
+    if (B.on && B.w * B.h > cap) {
+        const float f = sqrtf((float)cap / (float)(B.w * B.h));
+        const int w = max(1, (int)((float)B.w * f));
+        const int h = min(B.h, cap / w);
+        B.x0 = wrap_cell(B.x0 + (B.w - w) / 2, n, P.mask);
+        B.y0 = wrap_cell(B.y0 + (B.h - h) / 2, n, P.mask);
+        B.w = w;
+        B.h = h;
+    }
+    return B;
+}
+
+// R.nsteps reverse steps, newest first; tape[k np + p] is the position at the
+// start of step k.  lam holds NL adjoint vectors per particle (lam[p * NL +
+// r]), which stay in registers in between; gU (GRID) receives the grid
+// gradient of the first one.  Each step has its field tile, and, once its
+// stages are evaluated, the same LDS takes the block's contributions to the
+// grid gradient (gradient_box), which then go to gU with one atomic per nonzero
+// entry.  DET: gU holds fixed-point pairs (see to_fixed), and so does the box.
+//
+// Bound by its atomics and by latency at three waves per SIMD (165 registers;
+// at four, with 124 bytes a lane spilled, 11% slower).  2^22 lattice tracers on
+// 2048^2, bilinear: 417 -> 358 us a step with each stage's loads together, ->
+// 280 with the exact box (the box of the cells widened by the displacement
+// bound held 60% more nodes), the tile beside it and one read of the nodes for
+// velocity and Jacobian; 2^18 Catmull-Rom tracers on 1024^2, whose boxes
+// outgrew the fixed LDS: 1300 -> 130 us.
+template <int NL, bool GRID, bool CUBIC, bool DET>
+__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(CUBIC ? 2 : 3)))
+void adjoint64_kernel(StepParams P, StepRun R, const Rec64 *__restrict__ rec,
+                      const double2 *__restrict__ tape, int64_t np, double2 *__restrict__ lam,
+                      void *gU, int lds_bytes)
 {
     const int lb = blockIdx.x;
     const SpeciesDev &sp = P.sp[species_of(P, lb)];
@@ -323,176 +445,115 @@ __global__ __launch_bounds__(kMaxBlock) void adjoint64_kernel(StepParams P,
     const Rec64 *rec0 = rec + P.pitch + 1;
     const int scheme = sp.scheme;
     const double dt = P.dt, hdt = 0.5 * P.dt, dt6 = P.dt / 6.0, dt3 = P.dt / 3.0;
-    const double2 x = active ? tape[p] : make_double2(0.0, 0.0);
-    // LDS per box node: the field tile's two planes of (u, v) (32 bytes, when
-    // tiles are on), then the accumulators: three time levels x (u, v)
-    // doubles, or (DET) four (slot, component) planes of fixed-point pairs
-    // The box is sized for the accumulators (the scatter's atomics are what
-    // an oversized box sends to global memory); the tile is staged beside
-    // them only where both fit.
-    constexpr int kAccBytes = AGG ? (DET ? 64 : 48) : 0;
-    const bool tiles_on = P.tile_cap > 0;
-    const int box_bytes = AGG ? kAccBytes : (tiles_on ? 32 : 0);
-
-    GridGrad<DET> G{gU, adj_dyn_lds, no_tile()};
-    Tile T = no_tile();
     const double2 *planes = reinterpret_cast<const double2 *>(adj_dyn_lds);
-    if (box_bytes > 0) {
-        const int cap = lds_bytes / box_bytes;
-        const Loc64 me = locate64(P, x.x, x.y);
-        const double2 a0 = tape[sp.offset + base];
-        const Loc64 an = locate64(P, a0.x, a0.y);
-        int lo, hi;
-        stencil_reach(scheme, lo, hi);
-        const int H = step_halo(P, scheme, (float)dt);
-        Tile B = block_box(active, me.i, me.j, an.i, an.j, P.n, P.mask, lo + H, hi + H);
-        // a box beyond the LDS budget first loses halo, then rows: whatever
-        // falls outside it is read and added in global memory directly
-        int shrink = 0;
-        while (shrink < H && (B.w - 2 * shrink) * (B.h - 2 * shrink) > cap) ++shrink;
-        B.w -= 2 * shrink;
-        B.h -= 2 * shrink;
-        B.x0 = wrap_cell(B.x0 + shrink, P.n, P.mask);
-        B.y0 = wrap_cell(B.y0 + shrink, P.n, P.mask);
-        B.w = min(min(B.w, cap), P.n - 1);
-        B.h = min(min(B.h, cap / B.w), P.n - 1);
-        B.on = 1;
-        const int area = B.w * B.h;
-        const bool tiled = tiles_on && area * (32 + kAccBytes) <= lds_bytes;
-        if (tiled) {
-            T = B;
-            fill_tile_dma<Rec64>(reinterpret_cast<Rec64 *>(adj_dyn_lds), rec0, P, T);
-        }
-        if constexpr (AGG) {
-            G.B = B;
-            G.acc = adj_dyn_lds + (tiled ? 32 * area : 0);
-            const int words = (kAccBytes / 8) * area;
-            if constexpr (DET) {
-                unsigned long long *acc = static_cast<unsigned long long *>(G.acc);
-                for (int k = threadIdx.x; k < words; k += blockDim.x) acc[k] = 0ull;
-            } else {
-                double *acc = static_cast<double *>(G.acc);
-                for (int k = threadIdx.x; k < words; k += blockDim.x) acc[k] = 0.0;
-            }
-        }
-        __syncthreads();
+    int lo, hi;
+    stencil_reach(scheme, lo, hi);
+
+    double lx[NL][2];
+#pragma unroll
+    for (int r = 0; r < NL; ++r) {
+        const double2 l = active ? lam[p * NL + r] : make_double2(0.0, 0.0);
+        lx[r][0] = l.x;
+        lx[r][1] = l.y;
     }
+    for (int k = R.nsteps - 1; k >= 0; --k) {
+        const StageWeights &W = R.w[k];
+        const double2 *row = tape + (int64_t)k * np;
+        const double2 x = active ? row[p] : make_double2(0.0, 0.0);
+        const double2 a0 = row[sp.offset + base];
+        const int ax = cell_of_floor(floor(a0.x * P.invh), P.n, P.mask);
+        const int ay = cell_of_floor(floor(a0.y * P.invh), P.n, P.mask);
+        Tile T = no_tile();
+        if (P.tile_cap > 0)
+            T = tile64(P, sp, reinterpret_cast<Rec64 *>(adj_dyn_lds), rec0, x, active, ax, ay,
+                       base);
 
-    if (active) {
-        // forward recomputation of the stage points, exactly as the step kernel
-        double px[4], py[4];
-        double k1x, k1y, k2x, k2y, k3x, k3y;
-        px[0] = x.x;
-        py[0] = x.y;
-        vel64<CUBIC>(rec0, planes, T, P, scheme, px[0], py[0], P.w.wa[0], P.w.wb[0], P.w.smode[0],
-                     k1x, k1y);
-        px[1] = x.x + hdt * k1x;
-        py[1] = x.y + hdt * k1y;
-        vel64<CUBIC>(rec0, planes, T, P, scheme, px[1], py[1], P.w.wa[1], P.w.wb[1], P.w.smode[1],
-                     k2x, k2y);
-        px[2] = x.x + hdt * k2x;
-        py[2] = x.y + hdt * k2y;
-        vel64<CUBIC>(rec0, planes, T, P, scheme, px[2], py[2], P.w.wa[2], P.w.wb[2], P.w.smode[2],
-                     k3x, k3y);
-        px[3] = x.x + dt * k3x;
-        py[3] = x.y + dt * k3y;
-
-        // Back through x' = x + dt/6 (k1 + 2 k2 + 2 k3 + k4), k_q = U(x_q),
-        // x_q = x + c_q dt k_(q-1) (c = 1/2, 1/2, 1): per adjoint vector r,
-        // lx[r] collects dL/dx and lk[r][q] the adjoint of k_q; the stages are
-        // taken newest first, one stencil at a time.
-        double lx[NL][2], lk[NL][4][2];
+        // forward recomputation of the stage points, exactly as the step
+        // kernel, with the Jacobian at each
+        double px[4], py[4], J[4][4], lk[NL][4][2];
+        BoxAcc box = box_init();
+        if (active) {
+            double ku = 0.0, kv = 0.0;
+            const double ahead[4] = {0.0, hdt, hdt, dt};
 #pragma unroll
-        for (int r = 0; r < NL; ++r) {
-            const double2 l = lam[p * NL + r];
-            lx[r][0] = l.x;
-            lx[r][1] = l.y;
-            lk[r][0][0] = dt6 * l.x;
-            lk[r][0][1] = dt6 * l.y;
-            lk[r][1][0] = dt3 * l.x;
-            lk[r][1][1] = dt3 * l.y;
-            lk[r][2][0] = dt3 * l.x;
-            lk[r][2][1] = dt3 * l.y;
-            lk[r][3][0] = dt6 * l.x;
-            lk[r][3][1] = dt6 * l.y;
-        }
-        const bool grid = gU != nullptr;
-        const double back[4] = {0.0, hdt, hdt, dt};   // c_q dt
-#pragma unroll
-        for (int q = 3; q >= 0; --q) {
-            const Loc64 loc = locate64(P, px[q], py[q]);
-            const int grp = q == 0 ? 0 : (q == 3 ? 2 : 1);   // time level of the stage
-            double J[4];
-            if (!CUBIC || bilinear_at(P, scheme, loc)) {
-                const Sten64<2> st = stencil64<2>(scheme, loc);
-                if (grid)
-                    scatter64<2, DET>(G, P, st, grp, P.w.wa[q], P.w.wb[q], lk[0][q][0], lk[0][q][1]);
-                jacobian64<2>(rec0, planes, T, P, st, P.w.wa[q], P.w.wb[q], P.w.smode[q], J);
-            } else if constexpr (CUBIC) {
-                const Sten64<4> st = stencil64<4>(scheme, loc);
-                if (grid)
-                    scatter64<4, DET>(G, P, st, grp, P.w.wa[q], P.w.wb[q], lk[0][q][0], lk[0][q][1]);
-                jacobian64<4>(rec0, planes, T, P, st, P.w.wa[q], P.w.wb[q], P.w.smode[q], J);
+            for (int q = 0; q < 4; ++q) {
+                px[q] = q == 0 ? x.x : x.x + ahead[q] * ku;
+                py[q] = q == 0 ? x.y : x.y + ahead[q] * kv;
+                const Loc64 loc = locate64(P, px[q], py[q]);
+                if (!CUBIC || bilinear_at(P, scheme, loc))
+                    eval_stencil<2>(rec0, planes, T, P, stencil64<2>(scheme, loc), loc, W.wa[q],
+                                    W.wb[q], W.smode[q], ku, kv, J[q]);
+                else if constexpr (CUBIC)
+                    eval_stencil<4>(rec0, planes, T, P, stencil64<4>(scheme, loc), loc, W.wa[q],
+                                    W.wb[q], W.smode[q], ku, kv, J[q]);
+                if constexpr (GRID) {
+                    const BoxAcc c = box_of(loc.i, loc.j, ax, ay, P.n);
+                    box = q == 0 ? c : BoxAcc{pmax16(box.up, c.up), pmax16(box.dn, c.dn)};
+                }
             }
+            // Back through x' = x + dt/6 (k1 + 2 k2 + 2 k3 + k4), k_q = U(x_q),
+            // x_q = x + c_q dt k_(q-1) (c = 1/2, 1/2, 1): per adjoint vector r,
+            // lx[r] collects dL/dx and lk[r][q] the adjoint of k_q.
 #pragma unroll
             for (int r = 0; r < NL; ++r) {
-                double ls[2];
-                add_jt(J, lk[r][q], ls);
-                lx[r][0] += ls[0];
-                lx[r][1] += ls[1];
-                if (q > 0) {
-                    lk[r][q - 1][0] += back[q] * ls[0];
-                    lk[r][q - 1][1] += back[q] * ls[1];
-                }
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < NL; ++r) lam[p * NL + r] = make_double2(lx[r][0], lx[r][1]);
-    }
-
-    if constexpr (AGG) {
-        __syncthreads();
-        const int n = P.n, area = G.B.w * G.B.h;
-        const int64_t nn = (int64_t)n * n;
-        for (int k = threadIdx.x; k < area; k += blockDim.x) {
-            const int ty = k / G.B.w, tx = k - ty * G.B.w;
-            int gx = G.B.x0 + tx, gy = G.B.y0 + ty;
-            gx -= gx >= n ? n : 0;
-            gy -= gy >= n ? n : 0;
-            const int64_t g = (int64_t)gy * n + gx;
-            if constexpr (DET) {
-                const unsigned long long *acc = static_cast<const unsigned long long *>(G.acc);
-                unsigned long long *out = static_cast<unsigned long long *>(gU);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const unsigned long long hi = acc[2 * (q * area + k)];
-                    const unsigned long long lo = acc[2 * (q * area + k) + 1];
-                    if (hi | lo) {
-                        atomicAdd(out + 2 * (q * nn + g), hi);
-                        atomicAdd(out + 2 * (q * nn + g) + 1, lo);
-                    }
-                }
-            } else {
-                const double *acc = static_cast<const double *>(G.acc);
-                double *out = static_cast<double *>(gU);
-                // time levels 0, 1, 2 were taken at the weights of stages 0, 1, 3
-                const double wa[3] = {P.w.wa[0], P.w.wa[1], P.w.wa[3]};
-                const double wb[3] = {P.w.wb[0], P.w.wb[1], P.w.wb[3]};
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
-                    double s0 = 0.0, s1 = 0.0;
+                    lk[r][0][c] = dt6 * lx[r][c];
+                    lk[r][1][c] = dt3 * lx[r][c];
+                    lk[r][2][c] = dt3 * lx[r][c];
+                    lk[r][3][c] = dt6 * lx[r][c];
+                }
 #pragma unroll
-                    for (int g3 = 0; g3 < 3; ++g3) {
-                        const double v = acc[(2 * g3 + c) * area + k];
-                        s0 += wa[g3] * v;
-                        s1 += wb[g3] * v;
+                for (int q = 3; q >= 0; --q) {
+                    double ls[2];
+                    add_jt(J[q], lk[r][q], ls);
+                    lx[r][0] += ls[0];
+                    lx[r][1] += ls[1];
+                    if (q > 0) {
+                        lk[r][q - 1][0] += ahead[q] * ls[0];
+                        lk[r][q - 1][1] += ahead[q] * ls[1];
                     }
-                    if (s0 != 0.0) atomicAdd(out + c * nn + g, s0);
-                    if (s1 != 0.0) atomicAdd(out + (2 + c) * nn + g, s1);
                 }
             }
         }
+        if constexpr (GRID) {
+            // LDS per box node: three time levels x (u, v) doubles, or (DET)
+            // four (slot, component) planes of fixed-point pairs
+            constexpr int kNodeBytes = DET ? 64 : 48;
+            // every thread has read its tile when the box is known
+            GridGrad<DET> G{gU, adj_dyn_lds,
+                            gradient_box(box, ax, ay, P, lo, hi, lds_bytes / kNodeBytes)};
+            const int area = G.B.w * G.B.h;
+            if (G.B.on) {
+                const LdsU64 acc = (LdsU64)static_cast<unsigned long long *>(G.acc);
+                for (int w = threadIdx.x; w < (kNodeBytes / 8) * area; w += blockDim.x)
+                    acc[w] = 0ull;   // 0.0 too
+                __syncthreads();
+            }
+            if (active) {
+#pragma unroll
+                for (int q = 3; q >= 0; --q) {
+                    const Loc64 loc = locate64(P, px[q], py[q]);
+                    const int grp = q == 0 ? 0 : (q == 3 ? 2 : 1);   // time level of the stage
+                    if (!CUBIC || bilinear_at(P, scheme, loc))
+                        scatter64<2, DET>(G, P, stencil64<2>(scheme, loc), grp, W.wa[q], W.wb[q],
+                                          lk[0][q][0], lk[0][q][1]);
+                    else if constexpr (CUBIC)
+                        scatter64<4, DET>(G, P, stencil64<4>(scheme, loc), grp, W.wa[q], W.wb[q],
+                                          lk[0][q][0], lk[0][q][1]);
+                }
+            }
+            if (G.B.on) {
+                __syncthreads();
+                flush_box<DET>(G, P, W);
+                // the next step's first barrier (in its box) keeps the
+                // accumulators until every thread has flushed
+            }
+        }
     }
+    if (active)
+#pragma unroll
+        for (int r = 0; r < NL; ++r) lam[p * NL + r] = make_double2(lx[r][0], lx[r][1]);
 }
 
 // lam[p * NL + r] from the caller's per-id seeds: NL == 1: (gx[id], gy[id]);
@@ -551,56 +612,82 @@ __global__ void gather_adjoint_kernel(const uint32_t *__restrict__ id, int64_t n
     }
 }
 
-hipError_t launch_recompute64(const StepParams &P, const Rec64 *rec, const double2 *in,
-                              double2 *out, bool cubic, int block, hipStream_t st)
+hipError_t launch_recompute64(const StepParams &P, const StepRun &R, const Rec64 *rec,
+                              const double2 *in, double2 *tape, int64_t np, bool store_first,
+                              bool cubic, int block, hipStream_t st)
 {
     // the step kernel's tile: two planes of 16-byte entries, whole 64-entry chunks
     const size_t lds = P.tile_cap > 0 ? (size_t)(2 * P.tile_cap + kWave) * 16 : 0;
     if (cubic)
         hipLaunchKernelGGL(recompute64_kernel<true>, dim3(P.total_blocks), dim3(block), lds, st, P,
-                           rec, in, out);
+                           R, rec, in, tape, np, (int)store_first);
     else
         hipLaunchKernelGGL(recompute64_kernel<false>, dim3(P.total_blocks), dim3(block), lds, st,
-                           P, rec, in, out);
+                           P, R, rec, in, tape, np, (int)store_first);
     return hipGetLastError();
 }
 
-// LDS of the adjoint kernel: 31 KiB, so that five 256-thread blocks (the
-// bilinear kernel's register-bound occupancy) fit in a CU's 160 KiB.  The
-// accumulator box holds up to 661 nodes (48 bytes each; 496 of fixed-point
-// pairs), and the field tile joins it in boxes of up to 396 nodes (80
-// bytes each; 330 with fixed-point pairs); without accumulators, 992 nodes
-// of tile.
+// LDS of the adjoint kernel: 31 KiB, so that five 256-thread blocks fit in a
+// CU's 160 KiB: 960 nodes of field tile, then 661 nodes of gradient box (496 of
+// fixed-point pairs).  Where the particles of a block are spread over more cells
+// than that, the box takes what it needs, down to one block per CU.
 constexpr int kAdjLdsBytes = 31 * 1024;
 
-template <bool CUBIC, bool DET>
-static hipError_t launch_adjoint64_c(const StepParams &P, const Rec64 *rec, const double2 *tape,
-                                     double2 *lam, int nl, void *gU, int block, hipStream_t st)
+static int gradient_lds(const StepParams &P, int block, bool cubic, bool sorted, bool det)
 {
-    const size_t lds = kAdjLdsBytes + 64;   // the tile fill writes whole 16-byte pieces
-    if (nl == 1 && gU)
-        hipLaunchKernelGGL((adjoint64_kernel<1, true, CUBIC, DET>), dim3(P.total_blocks),
-                           dim3(block), lds, st, P, rec, tape, lam, gU, kAdjLdsBytes);
-    else if (nl == 1)
-        hipLaunchKernelGGL((adjoint64_kernel<1, false, CUBIC, false>), dim3(P.total_blocks),
-                           dim3(block), P.tile_cap > 0 ? lds : 0, st, P, rec, tape, lam,
-                           (void *)nullptr, kAdjLdsBytes);
-    else
-        hipLaunchKernelGGL((adjoint64_kernel<2, false, CUBIC, false>), dim3(P.total_blocks),
-                           dim3(block), P.tile_cap > 0 ? lds : 0, st, P, rec, tape, lam,
-                           (void *)nullptr, kAdjLdsBytes);
+    if (!sorted) return kAdjLdsBytes;   // boxes of any size: no use trying
+    double cells = 0.0;                 // of a block, at its species' density
+    for (int s = 0; s < P.nspecies; ++s)
+        cells = fmax(cells, (double)block * P.n * P.n / (double)P.sp[s].count);
+    const double side = sqrt(cells) + (cubic ? 8.0 : 6.0);
+    const double need = side * side * (det ? 64.0 : 48.0);
+    for (int per_cu = 5; per_cu >= 1; --per_cu) {
+        const int lds = (160 / per_cu - 1) * 1024;
+        if (need <= lds) return lds < kAdjLdsBytes ? kAdjLdsBytes : lds;
+    }
+    return kAdjLdsBytes;
+}
+
+template <int NL, bool GRID, bool CUBIC, bool DET>
+static hipError_t launch_adjoint64_t(const StepParams &P, const StepRun &R, const Rec64 *rec,
+                                     const double2 *tape, int64_t np, double2 *lam, void *gU,
+                                     int block, bool sorted, hipStream_t st)
+{
+    const int lds = GRID ? gradient_lds(P, block, CUBIC, sorted, DET) : kAdjLdsBytes;
+    StepParams Q = P;
+    // the tile's last fill chunk may run one chunk over
+    const int cap = (lds / 16 - kWave) / 2;
+    if (Q.tile_cap > cap) Q.tile_cap = cap;
+    hipLaunchKernelGGL((adjoint64_kernel<NL, GRID, CUBIC, DET>), dim3(P.total_blocks), dim3(block),
+                       GRID || P.tile_cap > 0 ? lds : 0, st, Q, R, rec, tape, np, lam, gU, lds);
     return hipGetLastError();
 }
 
-hipError_t launch_adjoint64(const StepParams &P, const Rec64 *rec, const double2 *tape,
-                            double2 *lam, int nl, void *gU, bool det, bool cubic, int block,
-                            hipStream_t st)
+template <bool CUBIC>
+static hipError_t launch_adjoint64_c(const StepParams &P, const StepRun &R, const Rec64 *rec,
+                                     const double2 *tape, int64_t np, double2 *lam, int nl,
+                                     void *gU, bool det, int block, bool sorted, hipStream_t st)
 {
-    if (det)
-        return cubic ? launch_adjoint64_c<true, true>(P, rec, tape, lam, nl, gU, block, st)
-                     : launch_adjoint64_c<false, true>(P, rec, tape, lam, nl, gU, block, st);
-    return cubic ? launch_adjoint64_c<true, false>(P, rec, tape, lam, nl, gU, block, st)
-                 : launch_adjoint64_c<false, false>(P, rec, tape, lam, nl, gU, block, st);
+    if (nl != 1)
+        return launch_adjoint64_t<2, false, CUBIC, false>(P, R, rec, tape, np, lam, nullptr, block,
+                                                          sorted, st);
+    if (!gU)
+        return launch_adjoint64_t<1, false, CUBIC, false>(P, R, rec, tape, np, lam, nullptr, block,
+                                                          sorted, st);
+    return det ? launch_adjoint64_t<1, true, CUBIC, true>(P, R, rec, tape, np, lam, gU, block,
+                                                          sorted, st)
+               : launch_adjoint64_t<1, true, CUBIC, false>(P, R, rec, tape, np, lam, gU, block,
+                                                           sorted, st);
+}
+
+hipError_t launch_adjoint64(const StepParams &P, const StepRun &R, const Rec64 *rec,
+                            const double2 *tape, int64_t np, double2 *lam, int nl, void *gU,
+                            bool det, bool cubic, int block, bool sorted, hipStream_t st)
+{
+    return cubic ? launch_adjoint64_c<true>(P, R, rec, tape, np, lam, nl, gU, det, block, sorted,
+                                            st)
+                 : launch_adjoint64_c<false>(P, R, rec, tape, np, lam, nl, gU, det, block, sorted,
+                                             st);
 }
 
 // Fixed-point pairs (hi 2^-32 + lo 2^-64) to binary64, in place order.

@@ -581,6 +581,23 @@ __device__ __forceinline__ void stencil_reach(int scheme, int &lo, int &hi)
     hi = scheme == kBilinear ? 1 : 2;
 }
 
+// Field tile of one logical block for one FP64 step: the box of its particles'
+// cells around the anchor cell (ax, ay), with the halo and the stencil's reach.
+__device__ __forceinline__ Tile tile64(const StepParams &P, const SpeciesDev &sp, Rec64 *lds,
+                                       const Rec64 *__restrict__ rec0, double2 x, bool active,
+                                       int ax, int ay, int64_t base)
+{
+    const int n = P.n, mask = P.mask;
+    const int cx = cell_of_floor(floor(x.x * P.invh), n, mask);
+    const int cy = cell_of_floor(floor(x.y * P.invh), n, mask);
+    int lo, hi;
+    stencil_reach(sp.scheme, lo, hi);
+    const int H = step_halo(P, sp.scheme, (float)P.dt);
+    const int64_t left = sp.count - base;
+    return stage_tile<Rec64>(lds, rec0, P, active, cx, cy, ax, ay, lo + H, hi + H,
+                             (int)(left < (int64_t)blockDim.x ? left : blockDim.x));
+}
+
 // ===========================================================================
 // FP64 path (physical units)
 // ===========================================================================
@@ -592,12 +609,6 @@ __device__ __forceinline__ void stencil_reach(int scheme, int &lo, int &hi)
 template <int SM>
 struct NodeRaw64 {
     double2 a, b;
-    __device__ __forceinline__ NodeRaw64() {}
-    __device__ __forceinline__ NodeRaw64(const double2 *q0, const double2 *q1)
-    {
-        a = SM == kSlot1 ? *q1 : *q0;
-        if constexpr (SM == kBlend) b = *q1;
-    }
     __device__ __forceinline__ void blend(double wa, double wb, double &u, double &v) const
     {
         if constexpr (SM == kBlend) {
@@ -632,22 +643,36 @@ struct RecNodes64 {
     __device__ __forceinline__ Raw<SM> load(int a, int b) const
     {
         const double2 *q = reinterpret_cast<const double2 *>(p + (b * pitch + a));
-        return Raw<SM>(q, q + 1);
+        Raw<SM> r;
+        r.a = SM == kSlot1 ? q[1] : q[0];
+        if constexpr (SM == kBlend) r.b = q[1];
+        return r;
     }
 };
 
 // Stencil nodes in the LDS tile: two planes of (u, v), level 0 then level 1,
-// `area` entries apart; node (a, b) at entry b pitch + a from p.
+// `area` entries apart; node (a, b) at entry b pitch + a from p.  (An LDS
+// pointer, not a generic one: where the compiler merges the code of the two
+// kinds of nodes it must not fall back to flat loads.)
+typedef const __attribute__((address_space(3))) f64x2 *LdsPair64;
+
 struct TileNodes64 {
     template <int SM>
     using Raw = NodeRaw64<SM>;
-    const double2 *p;
+    LdsPair64 p;
     int pitch, area;
     template <int SM>
     __device__ __forceinline__ Raw<SM> load(int a, int b) const
     {
-        const double2 *q = p + (b * pitch + a);
-        return Raw<SM>(q, q + area);
+        const LdsPair64 q = p + (b * pitch + a);
+        const f64x2 x = SM == kSlot1 ? q[area] : q[0];
+        Raw<SM> r;
+        r.a = make_double2(x.x, x.y);
+        if constexpr (SM == kBlend) {
+            const f64x2 y = q[area];
+            r.b = make_double2(y.x, y.y);
+        }
+        return r;
     }
 };
 
@@ -753,7 +778,7 @@ __device__ __forceinline__ void vel64(const Rec64 *__restrict__ rec0, const doub
     int t;
     if (!CUBIC || scheme == kBilinear || edge_cell(P.compat_edge, i, j, n)) {
         if (tile_index(T, i, j, 2, n, mask, t))
-            bil64(TileNodes64{tile + t, T.w, T.w * T.h}, xi, eta, smode, wa, wb, u, v);
+            bil64(TileNodes64{(LdsPair64)tile + t, T.w, T.w * T.h}, xi, eta, smode, wa, wb, u, v);
         else
             bil64(RecNodes64{rec0 + (__mul24(j, P.pitch) + i), P.pitch}, xi, eta, smode, wa, wb,
                   u, v);
@@ -772,7 +797,7 @@ __device__ __forceinline__ void vel64(const Rec64 *__restrict__ rec0, const doub
             cub64_quad(RecNodes64{rec0 + (__mul24(j - 1, P.pitch) + (i - 1)), P.pitch}, wx, wy,
                        smode, wa, wb, u, v);
         else if (tile_index(T, i - 1, j - 1, 4, n, mask, t))
-            cub64(TileNodes64{tile + t, T.w, T.w * T.h}, wx, wy, smode, wa, wb, u, v);
+            cub64(TileNodes64{(LdsPair64)tile + t, T.w, T.w * T.h}, wx, wy, smode, wa, wb, u, v);
         else
             cub64(RecNodes64{rec0 + (__mul24(j - 1, P.pitch) + (i - 1)), P.pitch}, wx, wy, smode,
                   wa, wb, u, v);

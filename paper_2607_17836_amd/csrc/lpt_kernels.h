@@ -230,15 +230,18 @@ hipError_t launch_order(const uint32_t *id, int64_t offset, int64_t count, int32
                         hipStream_t st);
 
 // reverse-mode derivatives of the FP64 tracer step (adjoint.hip); block is
-// the step kernel's block size (P's species block layout)
-hipError_t launch_recompute64(const StepParams &P, const Rec64 *rec, const double2 *in,
-                              double2 *out, bool cubic, int block, hipStream_t st);
+// the block size of P's species block layout.  tape: positions at the start
+// of consecutive steps, np apart; R: the steps' weights.
+hipError_t launch_recompute64(const StepParams &P, const StepRun &R, const Rec64 *rec,
+                              const double2 *in, double2 *tape, int64_t np, bool store_first,
+                              bool cubic, int block, hipStream_t st);
 // cubic: some species uses a bicubic scheme (else every stencil is bilinear).
 // det: gU holds fixed-point pairs of 64-bit words (4 n^2 pairs; value =
 // hi 2^-32 + lo 2^-64), summed exactly with integer atomics; else doubles.
-hipError_t launch_adjoint64(const StepParams &P, const Rec64 *rec, const double2 *tape,
-                            double2 *lam, int nl, void *gU, bool det, bool cubic, int block,
-                            hipStream_t st);
+// sorted: the particles were in cell order at the start of the segment.
+hipError_t launch_adjoint64(const StepParams &P, const StepRun &R, const Rec64 *rec,
+                            const double2 *tape, int64_t np, double2 *lam, int nl, void *gU,
+                            bool det, bool cubic, int block, bool sorted, hipStream_t st);
 // out[perm[i] * nl + r] = in[i * nl + r]: adjoint vectors back through a sort
 hipError_t launch_unpermute_adjoint(const uint32_t *perm, int64_t np, int nl, const double2 *in,
                                     double2 *out, hipStream_t st);

@@ -267,8 +267,10 @@ void free_sort(lpt_ctx *c)
     c->sw.capacity = 0;
 }
 
-StepParams make_params(const lpt_ctx *c)
+// block: the block size of the species' block layout (0: the step kernels').
+StepParams make_params(const lpt_ctx *c, int block = 0)
 {
+    if (block == 0) block = c->block;
     StepParams P{};
     P.n = c->n;
     P.pitch = (int32_t)padded_pitch(c->n);
@@ -297,7 +299,7 @@ StepParams make_params(const lpt_ctx *c)
         d.offset = h.offset;
         d.count = h.count;
         d.block_begin = blk;
-        blk += (int32_t)((h.count + c->block - 1) / c->block);
+        blk += (int32_t)((h.count + block - 1) / block);
         d.block_end = blk;
         d.x0_seed = h.x0_seed;
         d.x0_drawn = h.x0_drawn ? 1 : 0;
@@ -1390,6 +1392,9 @@ lpt_status lpt_forward_checkpointed(lpt_ctx *c, int64_t nsteps, double dt, int32
 
 namespace {
 
+// Up to this many particles the reverse sweep runs in blocks of one wave.
+constexpr int64_t kSweepWaves = 1 << 16;
+
 // Reverse sweep over the last checkpointed run: per segment, newest first,
 // rebuild the segment's per-step positions from its checkpoint, then take
 // the adjoint kernel back through them.
@@ -1400,38 +1405,45 @@ lpt_status reverse_sweep(lpt_ctx *c, int nl, double2 *&lam, double2 *&lam_spare,
     const int64_t tape_len = std::min(E, N);
     double2 *tape = nullptr;
     HIP_TRY(c, dalloc(tape, (size_t)(tape_len * np)));
-    StepParams P = make_params(c);
+    // few particles: one wave a block, so that they spread over the CUs
+    const int block = np <= kSweepWaves ? 64 : c->block;
+    StepParams P = make_params(c, block);
     set_dt(P, c->ck_dt);
-    // The sweep's LDS boxes (field tile, gradient accumulators) take the full
-    // displacement bound as their halo, so that a block's stage points stay
-    // inside them (an oversized box is trimmed by the kernels); a point
-    // outside costs global gathers and, in the adjoint, global atomics.
+    // The sweep's tiles take the full displacement bound as their halo, so that
+    // a block's stage points stay inside them (a point outside costs global
+    // gathers).
     P.halo_scale = 1.0f;
     const Rec64 *rec = static_cast<const Rec64 *>(c->rec);
+    StepRun R{};
+    // the weights of steps [k, k + m) of the run
+    auto weights = [&](int64_t k, int64_t m) {
+        R.nsteps = (int32_t)m;
+        for (int64_t j = 0; j < m; ++j) {
+            const StepWeights &w = c->ck_w[(size_t)(k + j)];
+            for (int q = 0; q < 4; ++q) {
+                R.w[j].wa[q] = w.wa[q];
+                R.w[j].wb[q] = w.wb[q];
+                R.w[j].smode[q] = slot_mode(w.wa[q], w.wb[q]);
+            }
+        }
+    };
     hipError_t e = hipSuccess;
     for (int64_t seg = (N - 1) / E; seg >= 0 && e == hipSuccess; --seg) {
         const int64_t k0 = seg * E, len = std::min(E, N - k0);
-        e = hipMemcpyAsync(tape, c->ck + seg * np, (size_t)np * sizeof(double2),
-                           hipMemcpyDeviceToDevice, c->stream);
-        for (int64_t s = 1; s < len && e == hipSuccess; ++s) {
-            const StepWeights &w = c->ck_w[(size_t)(k0 + s - 1)];
-            for (int q = 0; q < 4; ++q) {
-                P.w.wa[q] = w.wa[q];
-                P.w.wb[q] = w.wb[q];
-                P.w.smode[q] = slot_mode(w.wa[q], w.wb[q]);
-            }
-            e = launch_recompute64(P, rec, tape + (s - 1) * np, tape + s * np, c->has_cubic,
-                                   c->block, c->stream);
+        const double2 *start = c->ck + seg * np;
+        for (int64_t s = 0; s + 1 < len && e == hipSuccess; s += kMaxRun) {
+            const int64_t m = std::min<int64_t>(kMaxRun, len - 1 - s);
+            weights(k0 + s, m);
+            e = launch_recompute64(P, R, rec, s == 0 ? start : tape + s * np, tape + s * np, np,
+                                   s == 0, c->has_cubic, block, c->stream);
         }
-        for (int64_t s = len - 1; s >= 0 && e == hipSuccess; --s) {
-            const StepWeights &w = c->ck_w[(size_t)(k0 + s)];
-            for (int q = 0; q < 4; ++q) {
-                P.w.wa[q] = w.wa[q];
-                P.w.wb[q] = w.wb[q];
-                P.w.smode[q] = slot_mode(w.wa[q], w.wb[q]);
-            }
-            e = launch_adjoint64(P, rec, tape + s * np, lam, nl, gU, det, c->has_cubic,
-                                 c->block, c->stream);
+        // one step: its start is the checkpoint itself
+        const double2 *rows = len > 1 ? tape : start;
+        for (int64_t s1 = len; s1 > 0 && e == hipSuccess; s1 -= std::min<int64_t>(kMaxRun, s1)) {
+            const int64_t m = std::min<int64_t>(kMaxRun, s1), s0 = s1 - m;
+            weights(k0 + s0, m);
+            e = launch_adjoint64(P, R, rec, rows + s0 * np, np, lam, nl, gU, det, c->has_cubic,
+                                 block, c->ck_sorted, c->stream);
         }
         // back to the previous segment's slot order: the slot that segment
         // seg's sort filled from slot perm[i] gives its adjoint back there

@@ -33,23 +33,6 @@ __device__ __forceinline__ void advance_clock(const StepParams &P, int steps, De
     }
 }
 
-// Field tile of one logical block for one FP64 step: the box of its particles'
-// cells around the anchor cell (ax, ay), with the halo and the stencil's reach.
-__device__ __forceinline__ Tile tile64(const StepParams &P, const SpeciesDev &sp, Rec64 *lds,
-                                       const Rec64 *__restrict__ rec0, double2 x, bool active,
-                                       int ax, int ay, int64_t base)
-{
-    const int n = P.n, mask = P.mask;
-    const int cx = cell_of_floor(floor(x.x * P.invh), n, mask);
-    const int cy = cell_of_floor(floor(x.y * P.invh), n, mask);
-    int lo, hi;
-    stencil_reach(sp.scheme, lo, hi);
-    const int H = step_halo(P, sp.scheme, (float)P.dt);
-    const int64_t left = sp.count - base;
-    return stage_tile<Rec64>(lds, rec0, P, active, cx, cy, ax, ay, lo + H, hi + H,
-                             (int)(left < (int64_t)blockDim.x ? left : blockDim.x));
-}
-
 // One logical block of the FP64 run kernel: R.nsteps steps of the block's
 // particles, which stay in registers, with a new tile for each.  Slot p of D
 // takes the particle of slot p of S (D = S: in place), or, on the steps that
