@@ -33,8 +33,8 @@ __device__ __forceinline__ Loc64 locate64(const StepParams &P, double x, double 
     const double sx = x * P.invh, sy = y * P.invh;
     const double fx = floor(sx), fy = floor(sy);
     Loc64 l;
-    l.xi = sx - fx;
-    l.eta = sy - fy;
+    l.xi = sub_rn(sx, fx);
+    l.eta = sub_rn(sy, fy);
     l.i = cell_of_floor(fx, P.n, P.mask);
     l.j = cell_of_floor(fy, P.n, P.mask);
     return l;

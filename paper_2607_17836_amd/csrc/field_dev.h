@@ -15,7 +15,8 @@ namespace lpt {
 constexpr int kMaxBlock = 512;
 constexpr int kWave = 64;
 constexpr float kCellClampF = 1073741824.0f;   // 2^30 cells
-constexpr double kCellClampD = 1073741824.0;
+constexpr double kCellClampD = -1073741824.0;
+constexpr int kCellClampI = 1 << 30;
 
 // ---------------------------------------------------------------------------
 // Block order.  The hardware deals consecutive workgroups round-robin over the
@@ -179,11 +180,28 @@ __device__ __forceinline__ int cell_plus(int c, float fl, int n, int mask)
     return wrap_cell(c + (int)f, n, mask);
 }
 
+// Cell of a binary64 cell coordinate, within 2^30 cells of 0; a NaN goes to the
+// lower end, as v_max_f64 has it.  The conversion saturates on this hardware (a
+// C++ cast would leave that undefined), so the upper bound is an integer one.
+__device__ __forceinline__ int clamped_cell(double fl)
+{
+    int c;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(c) : "v"(fmax(fl, kCellClampD)));
+    return min(c, kCellClampI);
+}
+
+// a - b, rounded on its own: the in-cell coordinate is the difference of the
+// rounded product x n/L and its floor in every kernel, whether or not the
+// compiler sees the product next to it (fused, it would be another number).
+__device__ __forceinline__ double sub_rn(double a, double b)
+{
+#pragma clang fp contract(off)
+    return a - b;
+}
+
 __device__ __forceinline__ int cell_of_floor(double fl, int n, int mask)
 {
-    double f = fmin(fmax(fl, -kCellClampD), kCellClampD);
-    if (!(f == f)) f = 0.0;
-    return wrap_cell((int)f, n, mask);
+    return wrap_cell(clamped_cell(fl), n, mask);
 }
 
 // Catmull-Rom kernel (eq. cr_kernel) and cubic B-spline kernel
@@ -759,6 +777,15 @@ __device__ __forceinline__ void cub64_quad(const Nodes &N, const double wx[4], c
     v = quad_rows(wy, rv);
 }
 
+// Nodes of the stencil that starts `back` nodes before the periodic cell of (ci,
+// cj) on each axis, in global memory.
+__device__ __forceinline__ RecNodes64 record_nodes(const Rec64 *rec0, const StepParams &P, int ci,
+                                                   int cj, int back)
+{
+    const int i = wrap_cell(ci, P.n, P.mask) - back, j = wrap_cell(cj, P.n, P.mask) - back;
+    return RecNodes64{rec0 + (__mul24(j, P.pitch) + i), P.pitch};
+}
+
 // Velocity at (x, y) (physical units, any real value) with temporal weights
 // (wa, wb) on the two snapshot slots.  rec0 points at global node (0, 0);
 // tile/T is the block's LDS tile, two planes (T.on == 0: global only).
@@ -772,16 +799,18 @@ __device__ __forceinline__ void vel64(const Rec64 *__restrict__ rec0, const doub
 {
     const double sx = x * P.invh, sy = y * P.invh;
     const double fx = floor(sx), fy = floor(sy);
-    const double xi = sx - fx, eta = sy - fy;
+    const double xi = sub_rn(sx, fx), eta = sub_rn(sy, fy);
     const int n = P.n, mask = P.mask;
-    const int i = cell_of_floor(fx, n, mask), j = cell_of_floor(fy, n, mask);
+    // the cell before the periodic wrap: the tile needs only its distance from
+    // the tile's origin, wrapped
+    const int ci = clamped_cell(fx), cj = clamped_cell(fy);
     int t;
-    if (!CUBIC || scheme == kBilinear || edge_cell(P.compat_edge, i, j, n)) {
-        if (tile_index(T, i, j, 2, n, mask, t))
+    if (!CUBIC || scheme == kBilinear ||
+        (P.compat_edge && edge_cell(1, wrap_cell(ci, n, mask), wrap_cell(cj, n, mask), n))) {
+        if (tile_index(T, ci, cj, 2, n, mask, t))
             bil64(TileNodes64{(LdsPair64)tile + t, T.w, T.w * T.h}, xi, eta, smode, wa, wb, u, v);
         else
-            bil64(RecNodes64{rec0 + (__mul24(j, P.pitch) + i), P.pitch}, xi, eta, smode, wa, wb,
-                  u, v);
+            bil64(record_nodes(rec0, P, ci, cj, 0), xi, eta, smode, wa, wb, u, v);
         return;
     }
     if constexpr (CUBIC) {
@@ -794,13 +823,11 @@ __device__ __forceinline__ void vel64(const Rec64 *__restrict__ rec0, const doub
             weights_bs(eta, wy);
         }
         if constexpr (LANES == 4)
-            cub64_quad(RecNodes64{rec0 + (__mul24(j - 1, P.pitch) + (i - 1)), P.pitch}, wx, wy,
-                       smode, wa, wb, u, v);
-        else if (tile_index(T, i - 1, j - 1, 4, n, mask, t))
+            cub64_quad(record_nodes(rec0, P, ci, cj, 1), wx, wy, smode, wa, wb, u, v);
+        else if (tile_index(T, ci - 1, cj - 1, 4, n, mask, t))
             cub64(TileNodes64{(LdsPair64)tile + t, T.w, T.w * T.h}, wx, wy, smode, wa, wb, u, v);
         else
-            cub64(RecNodes64{rec0 + (__mul24(j - 1, P.pitch) + (i - 1)), P.pitch}, wx, wy, smode,
-                  wa, wb, u, v);
+            cub64(record_nodes(rec0, P, ci, cj, 1), wx, wy, smode, wa, wb, u, v);
     }
 }
 
