@@ -75,9 +75,8 @@ typedef struct {
 } ns2d_config;
 
 /* Create a context on the current HIP device: allocates the spectral state,
- * the AB2 history (both twice with the built-in transforms up to n = 1024),
- * four spectral and five grid work fields (about 11 n^2 doubles in total, 1.5
- * GB at n = 4096; 13 n^2 up to n = 1024) and either the twiddle table of the
+ * the AB2 history, four spectral and five grid work fields (about 11 n^2
+ * doubles in total, 1.5 GB at n = 4096) and either the twiddle table of the
  * built-in transforms or the three hipFFT plans and their work areas.
  * NS2D_E_ARG for a size or option outside the limits. */
 ns2d_status ns2d_create(const ns2d_config *cfg, ns2d_ctx **out);

@@ -40,7 +40,6 @@
 #include <cstdio>
 #include <new>
 #include <string>
-#include <utility>
 #include <vector>
 
 #include "fft_lds.h"
@@ -455,48 +454,49 @@ __global__ __launch_bounds__(N / 8) void column_emit_kernel(const double2 *__res
 }
 
 // column_fwd_kernel and column_emit_kernel of a step in one, for small grids:
-// the four blocks of a column each advance its state (the first one stores it,
-// into the other buffer: the rest may still be reading the old one) and take
-// one field back along y.  One launch and one trip through memory less for
-// three more transforms of a column.
+// four groups of N / 8 threads each advance the column's state and take one
+// field back along y.  The state stays where it is (a captured step can be
+// replayed): the first group stores it once all have read it.  One launch and
+// one trip through memory less for three more transforms of a column.
 template <int N, int MODE>
-__global__ __launch_bounds__(N / 8) void column_step_kernel(
-    const double2 *__restrict__ w_hat, const double2 *__restrict__ r_prev,
-    double2 *__restrict__ w_out, double2 *__restrict__ r_out, const double2 *__restrict__ specT,
-    double2 *__restrict__ fields, Spec S, const double2 *__restrict__ W)
+__global__ __launch_bounds__(N / 2) void column_step_kernel(double2 *w_hat, double2 *r_prev,
+                                                           const double2 *__restrict__ specT,
+                                                           double2 *__restrict__ fields, Spec S,
+                                                           const double2 *__restrict__ W)
 {
-    extern __shared__ double2 lds_col[];
+    extern __shared__ double2 lds_col[];   // a buffer per field
     constexpr int T = N / 8;
-    const int l = xcd_block(blockIdx.x, band_cols(N) * 4);
-    const int ix = l / 4, f = l % 4, t = threadIdx.x;
+    const int ix = blockIdx.x, f = threadIdx.x / T, t = threadIdx.x % T;
     const size_t col = (size_t)ix * N;
-    double2 v[8];
+    double2 *buf = lds_col + f * ns_fft::lds_entries<N>();
+    double2 v[8], w[8], r[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) v[q] = specT[col + t + q * T];
-    ns_fft::fft<N, false>(v, t, lds_col, W);
+    ns_fft::fft<N, false, false>(v, t, buf, W);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        advance_mode<N, MODE>(v[q], ix, t + q * T, S, w_hat, r_prev, col + t + q * T, w[q], r[q]);
+    __syncthreads();
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const int jy = t + q * T;
-        double2 w, r;
-        advance_mode<N, MODE>(v[q], ix, jy, S, w_hat, r_prev, col + jy, w, r);
         if (f == 0) {
-            w_out[col + jy] = w;
-            r_out[col + jy] = r;
+            w_hat[col + jy] = w[q];
+            r_prev[col + jy] = r[q];
         }
-        v[q] = field_mode(f, w, S.kscale * ix, S.kscale * signed_mode(jy, N), S.inv_nn);
+        v[q] = field_mode(f, w[q], S.kscale * ix, S.kscale * signed_mode(jy, N), S.inv_nn);
     }
-    ns_fft::fft<N, true>(v, t, lds_col, W);
+    ns_fft::fft<N, true, false>(v, t, buf, W);
     double2 *dst = fields + (size_t)f * S.plane + col;
 #pragma unroll
     for (int q = 0; q < 8; ++q) dst[t + q * T] = v[q];
 }
 
-// Grids up to kSmallGrid take rows_small_kernel (a group of N / 8 threads has to
-// stay inside a wave), up to kColumnStep column_step_kernel.  Us a step with the
-// general kernels and with these: n = 64 12.6 / 9.3, 256 15.4 / 11.6, 512 (both)
-// 24 / 16.4; 1024 (column_step_kernel) 41.0 / 39.1.  At 2048 its extra
-// transforms would cost three times column_fwd_kernel's 20 us.
-constexpr int kSmallGrid = 512, kColumnStep = 1024;
+// Grids up to kSmallGrid take rows_small_kernel and column_step_kernel (whose
+// groups of N / 8 threads have to stay inside a wave).  Us a step with the
+// general kernels and with these: n = 64 12.6 / 9.4, 256 15.4 /
+// 11.0, 512 24 / 15.4.
+constexpr int kSmallGrid = 512;
 
 template <int N>
 void launch_rows(bool store, const double2 *fields, size_t plane, double *grid, double2 *adv,
@@ -525,7 +525,6 @@ struct ns2d_ctx {
     double L = 0, nu = 0, dt = 0;
     double2 *spectra = nullptr;   // one allocation: the spectral planes that follow
     double2 *w_hat = nullptr, *r_prev = nullptr, *fields = nullptr;   // fields: 4 planes
-    double2 *w_next = nullptr, *r_next = nullptr;   // the other state (column_step_kernel)
     double *grid = nullptr;   // 4 grid fields: u, v, dw/dx, dw/dy (built-in path: u, v and,
                               // in place of the others, the x-transformed advection term)
     double *tmp = nullptr;    // grid scratch: advection term, read-back transforms
@@ -609,15 +608,13 @@ ns2d_status run_builtin_n(ns2d_ctx *c, BuiltinOp op)
         break;
     case kOpStep:
     case kOpLastStep:
-        if constexpr (N <= kColumnStep) {
+        if constexpr (N <= kSmallGrid) {
             if (c->first)
-                column_step_kernel<N, kColFirst><<<cols4, T, lds, st>>>(
-                    c->w_hat, c->r_prev, c->w_next, c->r_next, adv, c->fields, S, Wt);
+                column_step_kernel<N, kColFirst><<<cols, 4 * T, 4 * lds, st>>>(
+                    c->w_hat, c->r_prev, adv, c->fields, S, Wt);
             else
-                column_step_kernel<N, kColStep><<<cols4, T, lds, st>>>(
-                    c->w_hat, c->r_prev, c->w_next, c->r_next, adv, c->fields, S, Wt);
-            std::swap(c->w_hat, c->w_next);
-            std::swap(c->r_prev, c->r_next);
+                column_step_kernel<N, kColStep><<<cols, 4 * T, 4 * lds, st>>>(
+                    c->w_hat, c->r_prev, adv, c->fields, S, Wt);
         } else {
             if (c->first)
                 column_fwd_kernel<N, kColFirst><<<cols, T, lds, st>>>(c->w_hat, c->r_prev, adv, S, Wt);
@@ -701,8 +698,7 @@ ns2d_status ns2d_create(const ns2d_config *cfg, ns2d_ctx **out)
     };
     if (hipGetDevice(&c->device) != hipSuccess) return bail(NS2D_E_HIP);
     const size_t plane = (size_t)n * c->nh, cells = (size_t)n * n;
-    const bool two_states = own && n <= kColumnStep;
-    if (hipMalloc(&c->spectra, (two_states ? 8 : 6) * plane * sizeof(double2)) != hipSuccess ||
+    if (hipMalloc(&c->spectra, 6 * plane * sizeof(double2)) != hipSuccess ||
         hipMalloc(&c->grid, 4 * cells * sizeof(double)) != hipSuccess ||
         hipMalloc(&c->tmp, cells * sizeof(double)) != hipSuccess) {
         (void)hipGetLastError();
@@ -711,10 +707,6 @@ ns2d_status ns2d_create(const ns2d_config *cfg, ns2d_ctx **out)
     c->fields = c->spectra;
     c->w_hat = c->spectra + 4 * plane;
     c->r_prev = c->spectra + 5 * plane;
-    if (two_states) {
-        c->w_next = c->spectra + 6 * plane;
-        c->r_next = c->spectra + 7 * plane;
-    }
     // measured faster than hipFFT at the sizes compared (2048^2: 98 vs 337
     // us a step; 1024^2: 39 vs 101; 512^2: 16 vs 43)
     c->builtin = own;
