@@ -486,7 +486,9 @@ def ns_alg_bytes_per_step(n: int) -> int:
     transform; the spectral pass reads the transformed term, the state and
     the previous right-hand side and writes the state, the right-hand side
     and four spectral fields; the inverse transforms read the four fields
-    and write four grid fields."""
+    and write four grid fields.  (The count of a step whose row passes meet
+    on the grid; the built-in transforms fuse them and move 14 of these
+    spectra only.)"""
     spec = n * ((n - 1) // 3 + 1) * 16
     grid = n * n * 8
     return 4 * grid + spec + 9 * spec + 4 * (spec + grid)
@@ -530,8 +532,8 @@ def bench_ns(args, n=NS_N, dt=NS_DT):
            "k0": NS_K0, "omega_rms": NS_RMS, "precision": "fp64", "parallelism": "1 GPU"}
     roof = {"bound": "hbm", "achieved": ab / (step_us * 1e-6) / 1e9, "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": ab / (step_us * 1e-6) / 1e9 / HBM_PEAK_GBS, "traffic": None,
-            "kernel": ("whole field step: fwd_rows (product + x transform) + column (y transforms, AB2, "
-                      "4 fields) + inv_rows (x transforms), own LDS transforms" if builtin else
+            "kernel": ("whole field step: column kernels (y transforms, AB2, 4 fields) + rows_kernel (x "
+                      "transforms back, product, x transform), own LDS transforms" if builtin else
                       "whole field step: product + D2Z + spectral AB2 + batched Z2D (4 fields)"),
             "kernel_avg_us": step_us, "alg_bytes_per_step": ab}
     return args.steps / wall, 1e3 * wall / args.steps, cfg, roof
