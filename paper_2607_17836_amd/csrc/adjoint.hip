@@ -528,8 +528,10 @@ void adjoint64_kernel(StepParams P, StepRun R, const Rec64 *__restrict__ rec,
                 const LdsU64 acc = (LdsU64)static_cast<unsigned long long *>(G.acc);
                 for (int w = threadIdx.x; w < (kNodeBytes / 8) * area; w += blockDim.x)
                     acc[w] = 0ull;   // 0.0 too
-                __syncthreads();
             }
+            // the accumulators are clear; and, box or no box, every thread has
+            // read the box's reduction before the next one overwrites it
+            __syncthreads();
             if (active) {
 #pragma unroll
                 for (int q = 3; q >= 0; --q) {

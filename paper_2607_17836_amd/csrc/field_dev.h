@@ -420,8 +420,10 @@ __device__ __forceinline__ void wave_stats(double r2x, double r2y, bool active, 
 // always active), biased by 2^15 and packed two per word, as maxima of
 // (r + 2^15) and (2^15 - r).  A thread first folds its own particles into a
 // BoxAcc (box_add), then block_box_reduce combines the block's threads (all
-// threads must call it; it returns with the block synchronised) and fills
-// x0, y0, w, h of the result; `on` is left 0.
+// threads must call it) and fills x0, y0, w, h of the result; `on` is left 0.
+// Its one barrier comes before the threads read the combined words: what they
+// did before the call is done when it returns, but a caller that calls it again
+// has to synchronise the block in between.
 struct BoxAcc {
     uint32_t up, dn;
 };
