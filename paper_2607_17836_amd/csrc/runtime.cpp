@@ -1000,13 +1000,12 @@ lpt_status grow_records(lpt_ctx *c, int64_t nsteps, int32_t stats_every)
     return LPT_OK;
 }
 
-// Temporal weights of the step about to be taken (global number c->steps,
-// starting at c->t).
-void step_weights(const lpt_ctx *c, double dt, StageWeights &W)
+// Temporal weights of the step of global number `step` that starts at t.
+void step_weights(const lpt_ctx *c, int64_t step, double t, double dt, StageWeights &W)
 {
     const double stage_c[4] = {0.0, 0.5, 0.5, 1.0};
     for (int q = 0; q < 4; ++q) {
-        weights_at(c, c->steps, c->t, c->t + stage_c[q] * dt, dt, W.wa[q], W.wb[q]);
+        weights_at(c, step, t, t + stage_c[q] * dt, dt, W.wa[q], W.wb[q]);
         W.smode[q] = slot_mode(W.wa[q], W.wb[q]);
         W.waf[q] = (float)W.wa[q];
         W.wbf[q] = (float)W.wb[q];
@@ -1107,24 +1106,31 @@ lpt_status run_steps(lpt_ctx *c, int64_t nsteps, double dt, int32_t stats_every,
             if (ckpt) m = std::min<int64_t>(m, c->ck_every - k % c->ck_every);
         }
         R.nsteps = (int32_t)m;
+        // time and step number after the launch, which become the context's
+        // once it is enqueued: a launch that fails leaves them where they are
+        double t = c->t;
         for (int64_t j = 0; j < m; ++j) {
-            StageWeights &W = R.w[j];
-            step_weights(c, dt, W);
-            if (ckpt) {
+            step_weights(c, c->steps + j, t, dt, R.w[j]);
+            t += dt;
+        }
+        const int64_t steps = c->steps + m;
+        auto taken = [&]() {
+            for (int64_t j = 0; ckpt && j < m; ++j) {
                 StepWeights w;
                 for (int q = 0; q < 4; ++q) {
-                    w.wa[q] = W.wa[q];
-                    w.wb[q] = W.wb[q];
+                    w.wa[q] = R.w[j].wa[q];
+                    w.wb[q] = R.w[j].wb[q];
                 }
                 c->ck_w.push_back(w);
             }
-            c->t += dt;
-            c->steps += 1;
-        }
-        k += m;
-        const bool rec = stats_every > 0 && c->steps % stats_every == 0;
+            c->t = t;
+            c->steps = steps;
+            k += m;
+        };
+        const bool rec = stats_every > 0 && steps % stats_every == 0;
         if (!launch) {
             c->nrec += rec ? 1 : 0;
+            taken();
             continue;
         }
         P.w = R.w[0];
@@ -1189,6 +1195,7 @@ lpt_status run_steps(lpt_ctx *c, int64_t nsteps, double dt, int32_t stats_every,
             }
             c->nrec += 1;
         }
+        taken();
     }
     return LPT_OK;
 }
