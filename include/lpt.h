@@ -269,7 +269,13 @@ lpt_status lpt_set_state(lpt_ctx *ctx, const void *blob, size_t size);
  * statistics are summed per wave of 64 slots and merged in slot order, so the
  * block size and launch shape leave them unchanged too; a different sort
  * interval or sort key reorders the slots and so may change their last bits.
- * They are run-to-run reproducible for fixed choices. */
+ * They are run-to-run reproducible for fixed choices.
+ *
+ * tile_records, persistent, halo_scale, fused and rows shape the tiled step
+ * kernels.  While all five hold their defaults, populations that are too small to
+ * fill the GPU or too sparse to share a tile run kernels without any (workgroups
+ * of 64 slots, whatever the block size); any other value of one of them selects
+ * the tiled kernels for every population. */
 typedef struct {
     int32_t block_size;     /* particles (slots) per logical block of the step
                                kernel, 64, 128, 256 or 512 (0 selects 256);

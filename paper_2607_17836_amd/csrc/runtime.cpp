@@ -1031,8 +1031,14 @@ void step_weights(const lpt_ctx *c, int64_t step, double t, double dt, StageWeig
 // At 2^12 particles, n = 1024, a step took 10.2 (bilinear FP64) and 22.7 us
 // (bicubic FP64) in the tiled kernels: 5.1 and 6.5 us now, 2.2 and 3.3 us in
 // launches of 16.
+// A launch shape that the caller asked for belongs to the tiled kernels (a tile, a
+// halo, a cap on the workgroups, rows, species launches), so asking for one selects
+// them; the block size alone does not (both kinds lay the slots out by it).
 bool small_population(const lpt_ctx *c)
 {
+    const bool shaped = !c->tile_auto || c->persistent || c->rows != 1 || c->fused != 1 ||
+                        c->halo_scale != kHaloScaleDefault;
+    if (shaped) return false;
     const int64_t np = c->np, nn = (int64_t)c->n * c->n;
     if (c->has_cubic)
         return np <= 1 << 15 || (np <= 1 << 16 && 4 * np <= nn) || 16 * np <= nn;
