@@ -1021,13 +1021,20 @@ void step_weights(const lpt_ctx *c, int64_t step, double t, double dt, StageWeig
 // sparse for a block's tile to be shared.  Us a step, tiled / small, one step a
 // launch (and 16):
 //   bilinear FP64: n = 512, 2^18 particles 13.4 / 13.1 (9.8 / 9.6), 2^20 30.6 /
-//     31.3 (22.8 / 25.1); n = 4096, 2^20 126 / 104 (82 / 74), 2^22 200 / 229;
+//     31.3 (22.8 / 25.1); n = 2048, 2^19 34 / 32 (22 / 19); n = 4096, 2^20 110 /
+//     92 (72 / 64), 1.4e6 127 / 116 (75 / 73), 2^21 141 / 145 (78 / 83);
+//     n = 16384, n^2 / 16 1626 / 1459 (1027 / 1055), n^2 / 8 2086 / 2285 (1202 /
+//     1577); n = 32768, n^2 / 16 6545 / 5800 (4012 / 4162): where runs lose a few
+//     per cent, single steps (the streamed levels) gain ten;
 //   bilinear FP32: n = 1024, 2^18 13.1 / 11.4 (9.1 / 8.0), 2^19 16.0 / 15.9;
-//     n = 4096, 2^20 59 / 61 (54 / 48), 2^21 71 / 98;
+//     n = 4096, 2^20 59 / 61 (54 / 48), 2^21 71 / 98; n = 16384, 2^20 138 / 126
+//     (131 / 118);
 //   bicubic FP64: n = 512, 2^16 15.5 / 14.6 (13.0 / 11.6), 2^17 17.9 / 23.3;
-//     n = 1024, 2^18 32 / 42; n = 4096, 2^20 258 / 188, 2^22 339 / 519;
+//     n = 1024, 2^18 32 / 42; n = 4096, 2^20 258 / 188, 2^22 339 / 519; n^2 / 16 at
+//     n = 8192 965 / 707 (931 / 517), at 32768 14516 / 11115 (12440 / 8429);
 //   bicubic FP32: n = 512, 2^16 13.2 / 11.7, 2^17 14.3 / 17.4; n = 4096, 2^19
-//     102 / 64 (103 / 51), 2^20 109 / 108 (103 / 86), 2^21 129 / 185.
+//     102 / 64 (103 / 51), 2^20 109 / 108 (103 / 86), 2^21 129 / 185; n = 16384,
+//     n^2 / 16 2115 / 1712 (1482 / 1284).
 // At 2^12 particles, n = 1024, a step took 10.2 (bilinear FP64) and 22.7 us
 // (bicubic FP64) in the tiled kernels: 5.1 and 6.5 us now, 2.2 and 3.3 us in
 // launches of 16.
@@ -1043,7 +1050,8 @@ bool small_population(const lpt_ctx *c)
     if (c->has_cubic)
         return np <= 1 << 15 || (np <= 1 << 16 && 4 * np <= nn) || 16 * np <= nn;
     if (np <= 1 << 18) return true;
-    return c->precision == LPT_FP64 ? 8 * np <= nn : np <= 1 << 20 && 16 * np <= nn;
+    if (c->precision != LPT_FP64) return np <= 1 << 20 && 16 * np <= nn;
+    return 16 * np <= nn || (8 * np <= nn && np <= 3 << 19);
 }
 
 void set_dt(StepParams &P, double dt)

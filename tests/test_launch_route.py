@@ -7,12 +7,13 @@ import hip_stand_in
 
 SCRIPT = r"""
 precision, count, kw = sys.argv[2], int(sys.argv[3]), eval(sys.argv[4])
-tr = lpt.Tracker(16, precision, tile_records=kw.pop("created_with", 0))
-u = np.zeros((16, 16))
+n, schemes = kw.pop("n", 16), kw.pop("schemes", ("bilinear", "catmull_rom"))
+tr = lpt.Tracker(n, precision, tile_records=kw.pop("created_with", 0))
+u = np.zeros((n, n))
 tr.set_snapshot(0, 0.0, u, u)
 tr.set_snapshot(1, 1.0, u, u)
 x = np.linspace(0.0, 6.0, count)
-for scheme in ("bilinear", "catmull_rom"):
+for scheme in schemes:
     tr.add_species("tracer", 0.0, scheme, x, x)
 tr.set_tuning(**kw)
 launched()
@@ -49,3 +50,18 @@ def test_the_default_shape_leaves_small_populations_to_their_kernels(tmp_path, p
         assert "small64_kernel" in name or "small32_kernel" in name, name
     for name in _kernels(tmp_path, precision, 1 << 19, dict(kw)):
         assert "small" not in name, name
+
+
+@pytest.mark.parametrize("precision,scheme,n,count,small", [
+    ("fp64", "bilinear", 2048, 1 << 19, True),         # n^2 / 8
+    ("fp64", "bilinear", 2048, (1 << 19) + 1, False),
+    ("fp64", "bilinear", 3500, 3500 * 3500 // 8, True),
+    ("fp64", "bilinear", 4096, 1 << 21, False),        # n^2 / 8, too many
+    ("fp64", "bilinear", 16, 1 << 18, True),
+    ("fp32_split", "bilinear", 4096, 1 << 20, True),
+    ("fp32_split", "bilinear", 2048, (1 << 18) + 1, False),
+    ("fp64", "bspline", 1024, 1 << 16, True),          # n^2 / 16
+    ("fp64", "bspline", 1024, (1 << 16) + 1, False)])
+def test_the_population_line(tmp_path, precision, scheme, n, count, small):
+    for name in _kernels(tmp_path, precision, count, dict(n=n, schemes=(scheme,))):
+        assert ("small" in name) == small, name
