@@ -393,8 +393,15 @@ extern __shared__ __align__(32) unsigned char adj_dyn_lds[];
 
 // Box of the stencils of a block's stage points, for the gradient accumulators:
 // it holds every node they touch, unless that is more than `cap` nodes.  Then
-// it is cut down about its centre to a window that fits, or, beyond twice the
-// capacity, left out (B.on = 0): what falls outside goes to global memory.
+// it is cut down about its centre to a window that fits, or, beyond kBoxWaste
+// times the capacity, left out (B.on = 0): what falls outside goes to global
+// memory.  Windows of a sixteenth of the box still pay (2^22 unsorted lattice
+// tracers on 1024^2, 31 KiB: left out beyond twice the capacity 8125 us a reverse
+// step, beyond eight times 6428, never 6339); for one that holds hardly a stencil
+// the clearing and the flush are lost time (4096 unsorted particles on 1024^2: 20
+// us without a box, 22 with).
+constexpr int kBoxWaste = 16;
+
 __device__ __forceinline__ Tile gradient_box(BoxAcc b, int ax, int ay, const StepParams &P, int lo,
                                              int hi, int cap)
 {
@@ -402,7 +409,7 @@ __device__ __forceinline__ Tile gradient_box(BoxAcc b, int ax, int ay, const Ste
     Tile B = block_box_reduce(b, ax, ay, n, P.mask, lo, hi);
     B.w = min(B.w, n);
     B.h = min(B.h, n);
-    B.on = B.w * B.h <= 2 * cap;
+    B.on = B.w * B.h <= kBoxWaste * cap;   // at most 2^30 either side
     if (B.on && B.w * B.h > cap) {
         const float f = sqrtf((float)cap / (float)(B.w * B.h));
         const int w = max(1, (int)((float)B.w * f));
@@ -632,12 +639,17 @@ hipError_t launch_recompute64(const StepParams &P, const StepRun &R, const Rec64
 // LDS of the adjoint kernel: 31 KiB, so that five 256-thread blocks fit in a
 // CU's 160 KiB: 960 nodes of field tile, then 661 nodes of gradient box (496 of
 // fixed-point pairs).  Where the particles of a block are spread over more cells
-// than that, the box takes what it needs, down to one block per CU.
+// than that, the box takes what it needs, down to one block per CU.  Unsorted
+// particles spread over an unknown number: bound by the atomics that miss the box,
+// their blocks take the whole CU (2^22 lattice tracers on 2048^2 at 0.3 cells a
+// step: 31 KiB 2291 us a reverse step, 79 KiB 1347, 159 KiB 1019), except
+// one-wave blocks, which go four to a CU (2^14 lattice tracers on 64^2: 31 KiB
+// 25 us, 39 KiB 22; 4096 on 64^2: 39 KiB 20, 159 KiB 36).
 constexpr int kAdjLdsBytes = 31 * 1024;
 
 static int gradient_lds(const StepParams &P, int block, bool cubic, bool sorted, bool det)
 {
-    if (!sorted) return kAdjLdsBytes;   // boxes of any size: no use trying
+    if (!sorted) return (block == kWave ? 39 : 159) * 1024;
     double cells = 0.0;                 // of a block, at its species' density
     for (int s = 0; s < P.nspecies; ++s)
         cells = fmax(cells, (double)block * P.n * P.n / (double)P.sp[s].count);
