@@ -479,29 +479,40 @@ NS_N, NS_NU, NS_DT, NS_K0, NS_RMS, NS_SEED = 2048, 1e-4, 1e-3, 10.0, 3.0, 61
 
 
 def ns_alg_bytes_per_step(n: int) -> int:
-    """HBM bytes one field step must move at least.  Only the (n - 1) // 3 + 1
-    columns of a half spectrum inside the 2/3 band can be non-zero, so a
-    spectral array is n x that many complex doubles.  The advection term is
-    formed from the four grid fields (read once) inside the forward
-    transform; the spectral pass reads the transformed term, the state and
-    the previous right-hand side and writes the state, the right-hand side
-    and four spectral fields; the inverse transforms read the four fields
-    and write four grid fields.  (The count of a step whose row passes meet
-    on the grid; the built-in transforms fuse them and move 14 of these
-    spectra only.)"""
+    """HBM bytes one field step must move at least whose row passes meet on the
+    grid (library transforms).  Only the (n - 1) // 3 + 1 columns of a half
+    spectrum inside the 2/3 band can be non-zero, so a spectral array is n x
+    that many complex doubles.  The advection term is formed from the four grid
+    fields (read once) inside the forward transform; the spectral pass reads the
+    transformed term, the state and the previous right-hand side and writes the
+    state, the right-hand side and four spectral fields; the inverse transforms
+    read the four fields and write four grid fields."""
     spec = n * ((n - 1) // 3 + 1) * 16
     grid = n * n * 8
     return 4 * grid + spec + 9 * spec + 4 * (spec + grid)
+
+
+def ns_builtin_bytes_per_step(n: int, steps: int) -> float:
+    """The same for the built-in transforms, whose row pass goes from the four
+    spectral fields to the transformed advection term: the spectra alone, and the
+    velocity, which the last of a call's `steps` steps writes to the grid."""
+    spec = n * ((n - 1) // 3 + 1) * 16
+    return 9 * spec + 5 * spec + 2 * n * n * 8 / steps
+
+
+def ns_field_bytes(n: int, steps: int, builtin: bool) -> float:
+    """Bytes a step of a call of `steps` field steps, by its transforms."""
+    return ns_builtin_bytes_per_step(n, steps) if builtin else ns_alg_bytes_per_step(n)
 
 
 def bench_ns(args, n=NS_N, dt=NS_DT):
     """The Eulerian field producer on the n^2 grid in FP64 (2048^2, or 4096^2
     with dt = 5e-4: |k u| dt = 0.38 at the highest kept wavenumber):
     random-phase initial vorticity (k0 = 10, rms 3), nu = 1e-4; one step with
-    the library's own transforms = forward row pass (grid product and x
-    transforms), column pass (y transforms, AB2, the four fields) and
-    inverse row pass.  HIP events on the null stream, which the producer
-    runs on; the fields are checked finite afterwards."""
+    the library's own transforms = column pass (y transforms, AB2, the four
+    fields) and row pass (x transforms back, product, x transform).  HIP events
+    on the null stream, which the producer runs on; the fields are checked finite
+    afterwards."""
     import torch
     from paper_2607_17836_amd import lpt, ns2d, synth
     g = ns2d.Ns2d(n, NS_NU, dt)
@@ -526,7 +537,7 @@ def bench_ns(args, n=NS_N, dt=NS_DT):
     if not (np.isfinite(w).all() and np.isfinite(u).all()):
         raise RuntimeError(f"ns{n}: the flow left the stable range (non-finite fields)")
     step_us = 1e3 * ev_ms / args.steps
-    ab = ns_alg_bytes_per_step(n)
+    ab = ns_field_bytes(n, args.steps, builtin)
     log(f"[bench] ns{n}: {args.steps} steps in {wall:.3f} s; {step_us:.1f} us per step by events")
     cfg = {"workload": f"ns{n}_fp64_ab2_vorticity", "grid": n, "nu": NS_NU, "dt": dt,
            "k0": NS_K0, "omega_rms": NS_RMS, "precision": "fp64", "parallelism": "1 GPU"}
@@ -542,12 +553,14 @@ def bench_ns(args, n=NS_N, dt=NS_DT):
 COUPLED_PARTICLES, COUPLED_SEED = 1 << 20, 71
 
 
-def coupled_alg_bytes_per_step(n: int, particles: int) -> int:
-    """One coupled step: the field step, the ingest of the new level (u and v
-    read once, for the node records and the largest speed together; the
-    level's half of each 32-byte FP64 record written) and the FP64 tracer
-    step (state read and written, both levels of the field read once)."""
-    return (ns_alg_bytes_per_step(n) + 32 * n * n
+def coupled_alg_bytes_per_step(n: int, particles: int, field_bytes=None):
+    """One coupled step: the field step (`field_bytes`, by default that of the
+    library transforms), the ingest of the new level (u and v read once, for
+    the node records and the largest speed together; the level's half of each
+    32-byte FP64 record written) and the FP64 tracer step (state read and
+    written, both levels of the field read once)."""
+    field = ns_alg_bytes_per_step(n) if field_bytes is None else field_bytes
+    return (field + 32 * n * n
             + particles * 2 * state_bytes("fp64", "tracer", 0.0) + field_pair_bytes(n, "fp64"))
 
 
@@ -584,12 +597,13 @@ def bench_coupled(args):
         torch.cuda.synchronize()
         wall = time.perf_counter() - t0
         xw, yw, _, _ = loop.tracker.get_positions(sid)
+        builtin = loop.field.builtin
         loop.close()
         if not (np.isfinite(xw).all() and np.isfinite(yw).all()):
             raise RuntimeError("coupled2048: non-finite particle positions")
         out[streams] = (1e3 * e0.elapsed_time(e1) / steps, wall / steps)
     step_us, wall_step = out[1]
-    ab = coupled_alg_bytes_per_step(NS_N, COUPLED_PARTICLES)
+    ab = coupled_alg_bytes_per_step(NS_N, COUPLED_PARTICLES, ns_field_bytes(NS_N, 1, builtin))
     log(f"[bench] coupled2048: {step_us:.1f} us per coupled step on one stream, "
         f"{out[2][0]:.1f} us on two")
     cfg = {"workload": "coupled2048_fp64_ns_ab2_plus_2p20_tracers", "grid": NS_N,
