@@ -148,6 +148,7 @@ struct lpt_ctx {
     State64 s64[2]{};
     State32 s32[2]{};
     int cur = 0;
+    void *state_mem = nullptr;   // every array of the particle state (alloc_state)
     double2 *x0 = nullptr;   // initial positions, original order
     double2 *v0 = nullptr;   // given initial velocities, original order
     bool has_inertial = false, has_cubic = false;
@@ -224,36 +225,55 @@ int ilog2i(int64_t v)
     return s;
 }
 
-// The two arrays that hold a particle's position (pos and disp, or uc and
-// off) are one allocation, the second right behind the first, so that the
-// buffer a step is not using is also a scratch of one whole record per
-// particle (see readout).
-template <typename A, typename B>
-hipError_t alloc_pair(A *&a, B *&b, size_t count)
-{
-    static_assert(sizeof(A) == sizeof(B), "two arrays of one element size");
-    const hipError_t e = dalloc(a, 2 * count);
-    b = a ? reinterpret_cast<B *>(a + count) : nullptr;
-    return e;
-}
+// The particle state is one allocation (the allocator's cost goes by their
+// number, and by how often their sizes change): the two state buffers, then the
+// initial positions and velocities.  In a buffer the two arrays that hold a
+// particle's position (pos and disp, or uc and off) follow each other without a
+// gap, so that the buffer a step is not using is also a scratch of one whole
+// record per particle (see readout).  Two inertial FP32 species of 350 000
+// particles on 512^2, created, stepped four times, read and destroyed: 3800 us
+// with ten allocations, 5000 with the position pairs joined, 1150 to 2300 with one.
+struct StateArrays {
+    void *mem = nullptr;
+    State64 s64[2]{};
+    State32 s32[2]{};
+    double2 *x0 = nullptr, *v0 = nullptr;
+    size_t buffers = 0;   // bytes of the two state buffers, the first of mem
+};
 
-template <typename A, typename B>
-void free_pair(A *&a, B *&b)
+hipError_t alloc_state(StateArrays &a, int64_t np, bool fp64, bool vel)
 {
-    dfree(a);
-    b = nullptr;
-}
-
-void free_state(lpt_ctx *c)
-{
+    size_t size = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = size;
+        size += (bytes + 255) / 256 * 256;
+        return at;
+    };
+    const size_t n = (size_t)np, e = fp64 ? sizeof(double2) : sizeof(float2);
+    size_t pos[2], v[2] = {0, 0}, id[2];
     for (int k = 0; k < 2; ++k) {
-        free_pair(c->s64[k].pos, c->s64[k].disp);
-        dfree(c->s64[k].vel);
-        dfree(c->s64[k].id);
-        free_pair(c->s32[k].uc, c->s32[k].off);
-        dfree(c->s32[k].vel);
-        dfree(c->s32[k].id);
+        pos[k] = take(2 * n * e);
+        if (vel) v[k] = take(n * e);
+        id[k] = take(n * sizeof(uint32_t));
     }
+    a.buffers = size;
+    const size_t x0 = take(n * sizeof(double2)), v0 = vel ? take(n * sizeof(double2)) : 0;
+    char *m = nullptr;
+    const hipError_t err = dalloc(m, size);
+    if (err != hipSuccess) return err;
+    a.mem = m;
+    for (int k = 0; k < 2; ++k) {
+        if (fp64)
+            a.s64[k] = State64{(double2 *)(m + pos[k]), (double2 *)(m + pos[k]) + n,
+                               vel ? (double2 *)(m + v[k]) : nullptr, (uint32_t *)(m + id[k])};
+        else
+            a.s32[k] = State32{(int2 *)(m + pos[k]), (float2 *)(m + pos[k]) + n,
+                               vel ? (float2 *)(m + v[k]) : nullptr, (uint32_t *)(m + id[k]),
+                               (double2 *)(m + x0)};   // the displacement reference
+    }
+    a.x0 = (double2 *)(m + x0);
+    if (vel) a.v0 = (double2 *)(m + v0);
+    return hipSuccess;
 }
 
 void free_sort(lpt_ctx *c)
@@ -618,10 +638,8 @@ void lpt_destroy(lpt_ctx *c)
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    free_state(c);
+    dfree(c->state_mem);
     free_sort(c);
-    dfree(c->x0);
-    dfree(c->v0);
     dfree(c->partials);
     dfree(c->records);
     dfree(c->clock);
@@ -765,99 +783,51 @@ lpt_status init_species_state(lpt_ctx *c, int sid)
 lpt_status grow_state(lpt_ctx *c, int64_t np, int64_t old, bool inertial)
 {
     const bool fp64 = c->precision == LPT_FP64;
-    State64 n64[2]{};
-    State32 n32[2]{};
-    double2 *nx0 = nullptr, *nv0 = nullptr;
-    auto cleanup = [&]() {
-        for (int k = 0; k < 2; ++k) {
-            free_pair(n64[k].pos, n64[k].disp); dfree(n64[k].vel); dfree(n64[k].id);
-            free_pair(n32[k].uc, n32[k].off); dfree(n32[k].vel); dfree(n32[k].id);
-        }
-        dfree(nx0);
-        dfree(nv0);
-    };
-    bool ok = true;
-    const bool vel = inertial || c->has_inertial;
-    for (int k = 0; k < 2 && ok; ++k) {
-        if (fp64) {
-            ok = alloc_pair(n64[k].pos, n64[k].disp, np) == hipSuccess &&
-                 dalloc(n64[k].id, np) == hipSuccess &&
-                 (!vel || dalloc(n64[k].vel, np) == hipSuccess);
-        } else {
-            ok = alloc_pair(n32[k].uc, n32[k].off, np) == hipSuccess &&
-                 dalloc(n32[k].id, np) == hipSuccess &&
-                 (!vel || dalloc(n32[k].vel, np) == hipSuccess);
-        }
-    }
-    ok = ok && dalloc(nx0, np) == hipSuccess && (!vel || dalloc(nv0, np) == hipSuccess);
-    if (!ok) {
-        cleanup();
+    StateArrays a;
+    if (alloc_state(a, np, fp64, inertial || c->has_inertial) != hipSuccess) {
         (void)hipGetLastError();
         return fail(c, LPT_E_NOMEM, "device allocation of the particle state failed");
     }
-    {
-        // touch every page of both state buffers now, so that the first
-        // steps (whose re-sort writes the other buffer) meet no first-touch
-        // cost
-        hipError_t e = hipSuccess;
-        auto z = [&](void *d, size_t bytes) {
-            if (e == hipSuccess && d) e = hipMemsetAsync(d, 0, bytes, c->stream);
-        };
-        const size_t n = (size_t)np;
-        for (int k = 0; k < 2; ++k) {
-            if (fp64) {
-                z(n64[k].pos, n * sizeof(double2));
-                z(n64[k].disp, n * sizeof(double2));
-                z(n64[k].vel, n * sizeof(double2));
-                z(n64[k].id, n * sizeof(uint32_t));
-            } else {
-                z(n32[k].uc, n * sizeof(int2));
-                z(n32[k].off, n * sizeof(float2));
-                z(n32[k].vel, n * sizeof(float2));
-                z(n32[k].id, n * sizeof(uint32_t));
-            }
-        }
-        if (e != hipSuccess) {
-            cleanup();
-            return fail(c, LPT_E_HIP, std::string("state clear: ") + hipGetErrorString(e));
-        }
+    // touch every page of both state buffers now, so that the first steps (whose
+    // re-sort writes the other buffer) meet no first-touch cost
+    hipError_t e = hipMemsetAsync(a.mem, 0, a.buffers, c->stream);
+    if (e != hipSuccess) {
+        dfree(a.mem);
+        return fail(c, LPT_E_HIP, std::string("state clear: ") + hipGetErrorString(e));
     }
     if (old > 0) {
         const int k = c->cur;
-        hipError_t e = hipSuccess;
         auto cp = [&](void *d, const void *s, size_t bytes) {
             if (e == hipSuccess && s && d)
                 e = hipMemcpyAsync(d, s, bytes, hipMemcpyDeviceToDevice, c->stream);
         };
         if (fp64) {
-            cp(n64[k].pos, c->s64[k].pos, old * sizeof(double2));
-            cp(n64[k].disp, c->s64[k].disp, old * sizeof(double2));
-            cp(n64[k].vel, c->s64[k].vel, old * sizeof(double2));
-            cp(n64[k].id, c->s64[k].id, old * sizeof(uint32_t));
+            cp(a.s64[k].pos, c->s64[k].pos, old * sizeof(double2));
+            cp(a.s64[k].disp, c->s64[k].disp, old * sizeof(double2));
+            cp(a.s64[k].vel, c->s64[k].vel, old * sizeof(double2));
+            cp(a.s64[k].id, c->s64[k].id, old * sizeof(uint32_t));
         } else {
-            cp(n32[k].uc, c->s32[k].uc, old * sizeof(int2));
-            cp(n32[k].off, c->s32[k].off, old * sizeof(float2));
-            cp(n32[k].vel, c->s32[k].vel, old * sizeof(float2));
-            cp(n32[k].id, c->s32[k].id, old * sizeof(uint32_t));
+            cp(a.s32[k].uc, c->s32[k].uc, old * sizeof(int2));
+            cp(a.s32[k].off, c->s32[k].off, old * sizeof(float2));
+            cp(a.s32[k].vel, c->s32[k].vel, old * sizeof(float2));
+            cp(a.s32[k].id, c->s32[k].id, old * sizeof(uint32_t));
         }
-        cp(nx0, c->x0, old * sizeof(double2));
-        cp(nv0, c->v0, old * sizeof(double2));
+        cp(a.x0, c->x0, old * sizeof(double2));
+        cp(a.v0, c->v0, old * sizeof(double2));
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         if (e != hipSuccess) {
-            cleanup();
+            dfree(a.mem);
             return fail(c, LPT_E_HIP, std::string("state copy: ") + hipGetErrorString(e));
         }
     }
-    free_state(c);
-    dfree(c->x0);
-    dfree(c->v0);
+    dfree(c->state_mem);
+    c->state_mem = a.mem;
     for (int k = 0; k < 2; ++k) {
-        c->s64[k] = n64[k];
-        c->s32[k] = n32[k];
+        c->s64[k] = a.s64[k];
+        c->s32[k] = a.s32[k];
     }
-    c->x0 = nx0;
-    c->v0 = nv0;
-    c->s32[0].x0 = c->s32[1].x0 = nx0;   // the split state's displacement reference
+    c->x0 = a.x0;
+    c->v0 = a.v0;
     return LPT_OK;
 }
 
