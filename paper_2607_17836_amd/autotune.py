@@ -5,7 +5,9 @@ interval and key, persistent launches, fused or per-species step launches and
 hipGraph chunk length for one
 workload by timing candidates with HIP events on a throwaway context of that workload (``lpt_time_steps``), by
 coordinate descent from the library defaults.  None of these choices changes
-a per-particle result (see ``lpt_set_tuning``), only the time per step.
+a per-particle result (see ``lpt_set_tuning``), only the time per step.  Small
+populations run kernels of their own in the default shape, so for them every other
+tile, halo, launch or row setting is a trial of the tiled kernels instead.
 Results are cached in a JSON file keyed by the device, the grid, the
 precision and the species mix.  The package ships a table of tunings taken
 on MI355X (``tuned_mi355x.json``, written by ``python -m

@@ -430,8 +430,9 @@ __device__ __forceinline__ Tile gradient_box(BoxAcc b, int ax, int ay, const Ste
 // grid gradient (gradient_box), which then go to gU with one atomic per nonzero
 // entry.  DET: gU holds fixed-point pairs (see to_fixed), and so does the box.
 //
-// Bound by its atomics and by latency at three waves per SIMD (165 registers;
-// at four, with 124 bytes a lane spilled, 11% slower).  2^22 lattice tracers on
+// Bound by its atomics and by latency at three waves per SIMD (167 registers with
+// the grid gradient, 150-167 without; at four, with 124 bytes a lane spilled, 11%
+// slower) or, bicubic with the grid gradient, two (170).  2^22 lattice tracers on
 // 2048^2, bilinear: 417 -> 358 us a step with each stage's loads together, ->
 // 280 with the exact box (the box of the cells widened by the displacement
 // bound held 60% more nodes), the tile beside it and one read of the nodes for

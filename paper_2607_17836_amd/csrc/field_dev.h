@@ -419,7 +419,7 @@ __device__ __forceinline__ void wave_stats(double r2x, double r2y, bool active, 
 // offsets from (ax, ay), the cell of the block's first particle (which is
 // always active), biased by 2^15 and packed two per word, as maxima of
 // (r + 2^15) and (2^15 - r).  A thread first folds its own particles into a
-// BoxAcc (box_add), then block_box_reduce combines the block's threads (all
+// BoxAcc (box_of, pmax16), then block_box_reduce combines the block's threads (all
 // threads must call it) and fills x0, y0, w, h of the result; `on` is left 0.
 // Its one barrier comes before the threads read the combined words: what they
 // did before the call is done when it returns, but a caller that calls it again
@@ -448,13 +448,6 @@ __device__ __forceinline__ BoxAcc box_of(int cx, int cy, int ax, int ay, int n)
                   (uint32_t)(kBoxBias - rx) | ((uint32_t)(kBoxBias - ry) << 16)};
 }
 
-__device__ __forceinline__ void box_add(BoxAcc &b, int cx, int cy, int ax, int ay, int n)
-{
-    const BoxAcc c = box_of(cx, cy, ax, ay, n);
-    b.up = pmax16(b.up, c.up);
-    b.dn = pmax16(b.dn, c.dn);
-}
-
 __device__ __forceinline__ Tile block_box_reduce(BoxAcc b, int ax, int ay, int n, int mask,
                                                  int lo, int hi)
 {
@@ -481,15 +474,6 @@ __device__ __forceinline__ Tile block_box_reduce(BoxAcc b, int ax, int ay, int n
     T.x0 = wrap_cell(ax + mnx - lo, n, mask);
     T.y0 = wrap_cell(ay + mny - lo, n, mask);
     return T;
-}
-
-// The box of one particle per thread: (cx, cy) is the thread's cell
-// (ignored when !active).
-__device__ __forceinline__ Tile block_box(bool active, int cx, int cy, int ax, int ay, int n,
-                                          int mask, int lo, int hi)
-{
-    return block_box_reduce(active ? box_of(cx, cy, ax, ay, n) : box_init(), ax, ay, n, mask, lo,
-                            hi);
 }
 
 // Tile fill by LDS DMA: the tile's flat index space is cut into chunks of 64
@@ -549,9 +533,9 @@ __device__ __forceinline__ void fill_tile_dma(Rec *lds_rec, const Rec *__restric
 }
 
 // Cooperative tile set-up of one block (all threads must call it): the box
-// of the block's particles (folded into b by each thread, see box_add),
-// staged in LDS if it fits the capacity and is not much larger than the
-// block's particle count.
+// of the block's particles (folded into b by each thread), staged in LDS if
+// it fits the capacity and is not much larger than the block's particle count.
+// Ends with the block synchronised.
 template <typename Rec>
 __device__ __forceinline__ Tile stage_tile_acc(Rec *lds, const Rec *__restrict__ rec0,
                                               const StepParams &P, BoxAcc b, int ax, int ay,

@@ -127,8 +127,8 @@ struct State64 {
 // its residue mod n -- and the binary32 offset in [0, 1) cell units, so that
 // the position unwrapped since initialisation is (uc + off) h exactly and no
 // displacement is stored; binary32 velocity in cells per unit time.  16 bytes
-// a tracer, 24 an inertial particle, read and written once a step; the id is
-// moved only by the step after a re-sort.  x0: the initial positions by
+// a tracer, 24 an inertial particle, read and written once a launch; the id is
+// moved only by the launch after a re-sort.  x0: the initial positions by
 // original index (binary64, read by record steps and readout: the
 // displacement is (uc + off) - split(x0), in cells).
 struct State32 {

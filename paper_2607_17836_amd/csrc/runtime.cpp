@@ -365,7 +365,6 @@ int32_t slot_mode(double wa, double wb)
     return kBlend;
 }
 
-// The scheme every species uses, or 3 if they differ.
 int species_bits(const lpt_ctx *c) { return c->sp.size() > 1 ? ilog2i((int64_t)c->sp.size()) : 0; }
 int tile_bits(const lpt_ctx *c) { return 2 * ilog2i(c->n / c->sort_tile); }
 // Width of the cell-order key: species, tile and (with sort_cells) the cell

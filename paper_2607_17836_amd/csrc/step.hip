@@ -2,14 +2,15 @@
 // (FP64 and FP32-split), initial state, velocity probe, readout and the
 // statistics finalisation.
 //
-// One thread advances one particle by one RK4 step (Alg. coupled_EL, particle
-// loop; eqs. rk4_update / rk4_inertial).  Each of the four stages gathers the
-// 4 (bilinear) or 16 (bicubic) node records around the stage position; a node
-// record carries both retained time levels, so one gather serves the temporal
-// interpolation (eq. temporal_interp) too, and a stage whose temporal weight
-// is (1, 0) or (0, 1) loads only the half it needs.  Records carry a periodic
-// ghost border, so a stencil never wraps: its nodes are fixed offsets from one
-// base address.  State is structure-of-arrays with interleaved (x, y) pairs,
+// One thread advances one particle (two with rows = 2; four lanes one in the
+// small-population bicubic kernels) by a launch's RK4 steps, one or a run of
+// them (Alg. coupled_EL, particle loop; eqs. rk4_update / rk4_inertial).  Each of
+// the four stages gathers the 4 (bilinear) or 16 (bicubic) node records around
+// the stage position; a node record carries both retained time levels, so one
+// gather serves the temporal interpolation (eq. temporal_interp) too, and a stage
+// whose temporal weight is (1, 0) or (0, 1) loads only the half it needs.  Records
+// carry a periodic ghost border, so a stencil never wraps: its nodes are fixed
+// offsets from one base address.  State is structure-of-arrays with interleaved (x, y) pairs,
 // so the per-step state stream is fully coalesced; the gathers rely on
 // cell-ordered particles (sort.hip) and an XCD-aware block order for L2 reuse.
 #include "field_dev.h"
@@ -153,9 +154,10 @@ __device__ __forceinline__ void step64_block(const StepParams &P, const State64 
 
 // Bound by the latency of the stages' gathers, so by the waves that stay
 // resident: registers are bounded to six waves per SIMD for bilinear tracers
-// (76 registers; an 800-record tile leaves room for six blocks) and to four
-// otherwise (121-127; unbounded 133 and three waves).  With each stage's loads
-// in flight together (see blend64): 1024^2 Catmull-Rom, 2^20 tracers + 2^20
+// (80 registers, on record steps 24 bytes a lane of scratch; an 800-record tile
+// leaves room for six blocks) and to four otherwise (124-128; the bicubic
+// inertial bodies spill 16-28 bytes; unbounded 133 and three waves).  With each
+// stage's loads in flight together (see NodeRaw64): 1024^2 Catmull-Rom, 2^20 tracers + 2^20
 // inertial particles 136 -> 106 us a step; 2048^2, 2^20 bilinear tracers 58.9
 // -> 51.4 us; 4096^2, 2^24 bilinear tracers 421 -> 394 us with the shipped
 // 800-record tile, 479 -> 447 us with the default.
@@ -170,7 +172,9 @@ void step64_kernel(StepParams P, State64 S, const Rec64 *__restrict__ rec,
         step64_block<CUBIC, INERTIAL, STATS>(P, S, rec, partials, clock, lb);
 }
 
-// Runs of steps in one launch, and the step that follows a re-sort.
+// Runs of steps in one launch, and the step that follows a re-sort, in the same
+// bounds (bilinear tracers 79 registers and 20-36 bytes a lane of scratch, the
+// others 115-128 and up to 32).
 template <bool CUBIC, bool INERTIAL, bool STATS>
 __global__ __launch_bounds__(kMaxBlock)
 __attribute__((amdgpu_waves_per_eu(CUBIC || INERTIAL ? 4 : 6)))
@@ -834,13 +838,14 @@ __device__ __forceinline__ void step32_block(const StepParams &P, const StepRun 
     if (lb == 0) advance_clock(P, nsteps, clock);
 }
 
-// One launch advances every particle of its logical blocks by one step
+// One launch advances every particle of its logical blocks by one step in place
 // (block_walk: one workgroup per logical block in XCD-aware order, a
 // persistent walk, or a fused launch's block-order table).
 // Bilinear blocks hold eight 256-thread blocks per CU (the LDS tile's
 // budget), i.e. eight waves per SIMD, so their registers are bounded to fit
-// that; the bicubic bodies, and the fused kernel that holds every body
-// (SCHS = kAnyScheme), need more registers and keep the default bound.
+// that (49-63); the bicubic bodies, and the fused kernel that holds every body
+// (SCHS = kAnyScheme), need more and are bounded to six (73-80; inertial ones
+// spill up to 40 bytes a lane, in the run kernels below up to 48).
 template <int SCHS, int KINDS, bool STATS, int ROWS>
 __global__ __launch_bounds__(kMaxBlock)
 __attribute__((amdgpu_waves_per_eu(SCHS == kBilinear ? 8 : 6, SCHS == kBilinear ? 8 : 6)))
@@ -868,16 +873,16 @@ void run32_kernel(StepParams P, StepRun R, State32 S, State32 D, const uint32_t 
 
 // ===========================================================================
 // Runs of steps for populations too small to fill the chip, or too sparse to
-// share a tile.  Such a launch lasts as long as one wave's chain of dependent gathers, plus
-// the launch itself, whatever the number of particles, so the particles keep
-// their state in registers for up to kMaxRun steps (to the next record,
+// share a tile.  Such a launch lasts as long as one wave's chain of dependent
+// gathers, plus the launch itself, whatever the number of particles, so the
+// particles keep their state in registers for up to kMaxRun steps (to the next record,
 // re-sort or checkpoint), every wave has a CU to itself where there are
 // enough (workgroups of 64 slots), and a bicubic stencil is split by rows
 // over four lanes, which quarters the loads of the chain.  No LDS tile: the
 // few particles of a workgroup share no nodes worth staging.  Each unit of 64
 // slots is one statistics partial, as in the other step kernels, and every
 // sum is taken in their order, so the results are the same bits.  4096
-// particles, 64^2, 100 steps with 10 records: 868 -> 395 us a call; which
+// particles, 64^2, 100 steps with 10 records: 911 -> 365 us a call; which
 // populations count as small is decided where these are launched.
 // ===========================================================================
 template <int LANES>
