@@ -10,7 +10,7 @@ the particle step may overlap; two events keep the hand-off in order: the
 particle stream waits for the new level before ingesting it, and the field
 stream waits for that ingest before its next step overwrites the velocity
 buffers.  Measured at 2048^2 with 2^20 FP64 tracers, the overlap is slower
-(329 against 298 us a coupled step): both phases contend for HBM and L2.
+(241 against 228 us a coupled step): both phases contend for HBM and L2.
 """
 from __future__ import annotations
 
